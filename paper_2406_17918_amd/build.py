@@ -1,13 +1,16 @@
-"""Build the C-ABI HIP library (``libgss.so``) for gfx950, in-tree next to its sources."""
+"""Build the C-ABI HIP library (``libgss.so``) for gfx950 and the binding's CPython module (``gss_torch.so``), in-tree
+next to their sources."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libgss.so")
+BINDING_PATH = os.path.join(_HERE, "gss_torch.so")
 SOURCES = ["gss_kernels.hip", "gss_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -24,5 +27,20 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+def build_binding(verbose: bool = False) -> str:
+    """Compile ``csrc/gss_torch.cpp`` against PyTorch's headers (host code only; always recompiles)."""
+    import torch
+    base = os.path.dirname(os.path.abspath(torch.__file__))
+    inc, lib = os.path.join(base, "include"), os.path.join(base, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-isystem", inc,
+           "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "gss_torch.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return BINDING_PATH
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_binding(verbose=True))

@@ -14,6 +14,7 @@ from typing import Dict, List, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgss.so")
+BINDING_PATH = os.path.join(_HERE, "gss_torch.so")
 
 GSS_OK, GSS_ERR_INVALID_ARG, GSS_ERR_INVALID_GRAPH, GSS_ERR_INVALID_SEED = 0, 1, 2, 3
 GSS_ERR_OOM, GSS_ERR_DEVICE, GSS_ERR_STEP_ORDER = 4, 5, 6
@@ -124,6 +125,22 @@ def load_library():
     return L
 
 
+_native = None
+
+
+def load_binding():
+    """The CPython module of the hot calls (``csrc/gss_torch.cpp``): marshals a step's arguments and makes its tensors in C++."""
+    global _native
+    if _native is None:
+        lib = load_library()
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{BINDING_PATH} not found: build it with `python -m paper_2406_17918_amd.build`")
+        from . import gss_torch
+        gss_torch.bind(*(C.cast(f, C.c_void_p).value for f in (lib.gss_step, lib.gss_step_async, lib.gss_step_wait, lib.gss_gather_rows)))
+        _native = gss_torch
+    return _native
+
+
 class GssError(RuntimeError):
     def __init__(self, status: int, msg: str):
         super().__init__(f"gss status {status}: {msg}")
@@ -193,17 +210,10 @@ def gather_rows(table, ids, out=None):
     """gss_gather_rows on torch tensors: out[i] = table[ids[i]] (table: [N, ...] contiguous, ids: int32, both on the GPU);
     enqueued on torch's current stream."""
     import torch
-    assert table.is_cuda and ids.is_cuda and ids.dtype == torch.int32 and table.is_contiguous() and ids.is_contiguous()
-    n = ids.numel()
     if out is None:
-        out = torch.empty((n,) + tuple(table.shape[1:]), dtype=table.dtype, device=table.device)
-    assert out.is_contiguous() and out.dtype == table.dtype and out.numel() * table.shape[0] == n * table.numel()
-    row_bytes = table.element_size()
-    for d in table.shape[1:]:
-        row_bytes *= int(d)
-    st = load_library().gss_gather_rows(table.data_ptr() if table.numel() else None, table.shape[0], row_bytes,
-                                        ids.data_ptr() if n else None, n, out.data_ptr() if n else None,
-                                        torch.cuda.current_stream(table.device).cuda_stream)
+        out = torch.empty((ids.numel(),) + tuple(table.shape[1:]), dtype=table.dtype, device=table.device)
+    native = _native or load_binding()
+    st = native.gather_rows(table, ids, out, torch._C._cuda_getCurrentRawStream(table.device.index) if table.is_cuda else 0)
     if st != GSS_OK:
         raise GssError(st, "gss_gather_rows failed")
     return out
@@ -246,15 +256,18 @@ class Sampler:
         st = self._lib.gss_create_tuned(C.byref(g), C.byref(cfg), C.byref(tn), C.byref(h))
         if st != GSS_OK:
             raise GssError(st, "gss_create failed: " + self._lib.gss_last_error(None).decode())
-        self._h = h
+        self._h, self._handle = h, h.value
         self.pipeline_depth = int(self._lib.gss_pipeline_depth(h))   # steps that may be in flight
         self._blocks = gss_blocks()
-        self._fo_cache = {}
+        self._native = load_binding()
+        # (an allocator that makes its own views of its memory gets to make the blocks' tensors)
+        self._own_views = getattr(type(self._allocator), "view_i32", None) is not _TorchAllocator.view_i32
+        self._empty = torch.empty(0, dtype=torch.int32, device=self.device)
 
     def close(self):
         if getattr(self, "_h", None):
             self._lib.gss_destroy(self._h)
-            self._h = None
+            self._h, self._handle = None, 0
 
     def __del__(self):
         try:
@@ -271,19 +284,10 @@ class Sampler:
             raise GssError(st, self._lib.gss_last_error(self._h).decode())
         return self._blocks
 
-    def _fanout_array(self, fanouts):
-        key = tuple(fanouts)
-        fo = self._fo_cache.get(key)
-        if fo is None:
-            fo = self._fo_cache[key] = (C.c_int32 * len(key))(*key)
-        return fo
-
     def step_async(self, seeds, fanouts: Sequence[int], step: int, seed_type: int = 0) -> None:
         """gss_step_async: enqueue one step (at most `pipeline_depth` may be in flight); `seeds` must outlive it."""
-        fo = self._fanout_array(fanouts)
-        n = seeds.numel()
-        st = self._lib.gss_step_async(self._h, seeds.data_ptr() if n else None, n, seed_type, fo, len(fanouts), step)
-        if st != GSS_OK:
+        st = self._native.step_async(self._handle, seeds, fanouts, step, seed_type)
+        if st:
             raise GssError(st, self._lib.gss_last_error(self._h).decode())
 
     def step_wait_raw(self) -> gss_blocks:
@@ -294,10 +298,23 @@ class Sampler:
         return self._blocks
 
     def step_wait(self) -> List[Block]:
-        return self._wrap(self.step_wait_raw())
+        if self._own_views:
+            return self._wrap(self.step_wait_raw())
+        return self._checked(self._native.step_wait, self._handle, self._allocator.live, Block, self._empty)
 
     def step(self, seeds, fanouts: Sequence[int], step: int, seed_type: int = 0) -> List[Block]:
-        return self._wrap(self.step_raw(seeds, fanouts, step, seed_type))
+        if self._own_views:
+            return self._wrap(self.step_raw(seeds, fanouts, step, seed_type))
+        return self._checked(self._native.step, self._handle, seeds, fanouts, step, seed_type, self._allocator.live, Block, self._empty)
+
+    def _checked(self, call, *args) -> List[Block]:
+        try:
+            out = call(*args)
+        except ValueError as e:            # (an output that does not fit its allocation)
+            raise GssError(GSS_ERR_DEVICE, str(e)) from None
+        if out.__class__ is int:
+            raise GssError(out, self._lib.gss_last_error(self._h).decode())
+        return out
 
     def _wrap(self, b) -> List[Block]:
         T, R = b.num_node_types, b.num_relations
