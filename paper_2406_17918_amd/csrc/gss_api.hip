@@ -25,6 +25,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -82,12 +83,83 @@ struct EventTimer : LaunchTimer {
   ~EventTimer() override { collect(); for (hipEvent_t e : pool_) (void)hipEventDestroy(e); }
 };
 
+// What a sampler needs of the HIP runtime besides device memory: its streams, events and pinned host words.  They take
+// long to make (a stream 150 us, a pinned allocation 23 us and 52 us to free, measured) and do not depend on the graph, so
+// a destroyed sampler leaves them - idle - to the next one of the same device; they live until the process ends.
+struct HostKit {
+  int device = -1;
+  hipStream_t work = nullptr, fill_stream = nullptr;      // fill_stream: made when a sampler first needs it
+  hipEvent_t user_ready = nullptr, fill_go = nullptr, fill_done = nullptr;
+  hipEvent_t tick_ev[TICK_EVENTS] = {};
+  char* pinned = nullptr;
+  char* pinned_dev = nullptr;                             // the same memory as the device sees it
+  size_t pinned_bytes = 0;
+};
+constexpr size_t MAX_IDLE_KITS = 8;
+std::mutex g_kits_lock;
+std::vector<HostKit*> g_kits;
+
+void free_kit(HostKit* k) {
+  if (!k) return;
+  if (k->work) (void)hipStreamDestroy(k->work);
+  if (k->fill_stream) (void)hipStreamDestroy(k->fill_stream);
+  for (hipEvent_t ev : {k->user_ready, k->fill_go, k->fill_done}) if (ev) (void)hipEventDestroy(ev);
+  for (hipEvent_t ev : k->tick_ev) if (ev) (void)hipEventDestroy(ev);
+  if (k->pinned) (void)hipHostFree(k->pinned);
+  delete k;
+}
+
+hipError_t take_kit(size_t pinned_bytes, HostKit** out) {
+  *out = nullptr;
+  int device = -1;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  {
+    std::lock_guard<std::mutex> lock(g_kits_lock);
+    for (size_t i = 0; i < g_kits.size(); ++i)
+      if (g_kits[i]->device == device && g_kits[i]->pinned_bytes >= pinned_bytes) {
+        *out = g_kits[i];
+        g_kits.erase(g_kits.begin() + (std::ptrdiff_t)i);
+        return hipSuccess;
+      }
+  }
+  HostKit* k = new (std::nothrow) HostKit();
+  if (!k) return hipErrorOutOfMemory;
+  k->device = device;
+  auto event = [&](hipEvent_t* ev) { if (e == hipSuccess && (e = hipEventCreateWithFlags(ev, hipEventDisableTiming)) != hipSuccess) *ev = nullptr; };
+  if ((e = hipStreamCreateWithFlags(&k->work, hipStreamNonBlocking)) != hipSuccess) k->work = nullptr;
+  event(&k->user_ready); event(&k->fill_go); event(&k->fill_done);
+  for (hipEvent_t& ev : k->tick_ev) event(&ev);
+  if (e == hipSuccess) {
+    e = hipHostMalloc((void**)&k->pinned, pinned_bytes, hipHostMallocDefault);
+    if (e != hipSuccess) k->pinned = nullptr;
+    else if ((e = hipHostGetDevicePointer((void**)&k->pinned_dev, k->pinned, 0)) == hipSuccess) k->pinned_bytes = pinned_bytes;
+  }
+  if (e != hipSuccess) { free_kit(k); return e; }
+  *out = k;
+  return hipSuccess;
+}
+
+// (its streams must be idle)
+void leave_kit(HostKit* k) {
+  if (!k) return;
+  {
+    std::lock_guard<std::mutex> lock(g_kits_lock);
+    if (g_kits.size() < MAX_IDLE_KITS) {
+      try { g_kits.push_back(k); return; } catch (...) {}
+    }
+  }
+  free_kit(k);
+}
+
 // Everything one step in flight owns.
 struct Slot {
   int32_t* state_d = nullptr;
   int32_t* state_h = nullptr;            // pinned copy of the device state, written by the last emit phase
   int32_t* state_h_dev = nullptr;        // the same memory as the device sees it
-  Buf hash, direct, picks, order, ranks, partial_first, partial_edge, first_off, edge_off;
+  Buf hash, direct, scratch;             // dedupe table (either layout); what the phases of a step hand to each other:
+  int32_t *picks = nullptr, *partial_first = nullptr, *partial_edge = nullptr, *first_off = nullptr, *edge_off = nullptr;
+  uint32_t *order = nullptr, *ranks = nullptr;   // ... parts of `scratch`
   Buf visit, held, list, counts;         // visit-once steps: visit table (8 bytes per node), holding area, node lists and their counters
   int chain_parity = 0;                  // which of the two counter sets the slot's next visit-once step uses
   uint32_t ver = VERSION_FIRST;          // next unused dedupe table version
@@ -95,7 +167,6 @@ struct Slot {
   Buf src_local[GSS_MAX_LAYERS][GSS_MAX_RELATIONS], dst_local[GSS_MAX_LAYERS][GSS_MAX_RELATIONS];
   hipEvent_t done = nullptr;             // completes when the step's last phase has run (the event of that tick, borrowed)
   bool pending = false;                  // enqueued and not yet collected
-  bool used = false;                     // has held a step: its output buffers may still be read by the caller
   int L = 0, num_seeds = 0, seed_type = 0;
   // plan of the step the slot holds (host-known upper bounds of every hop)
   const int32_t* seeds = nullptr;
@@ -116,6 +187,15 @@ struct Slot {
   std::vector<gss_block_nodes> out_nodes;
   std::vector<gss_block_edges> out_edges;
 };
+
+// Sizes of a step's buffers (outputs by layer): the largest of the steps planned so far is what a slot's buffers grow to.
+struct StepSizes {
+  int L = 0;
+  int64_t src[GSS_MAX_LAYERS][GSS_MAX_NODE_TYPES] = {};
+  int64_t edges[GSS_MAX_LAYERS][GSS_MAX_RELATIONS] = {};
+  int64_t slots = 0, keys = 0;           // pick slots of a hop (whole tiles), dedupe keys
+  size_t held = 0, list = 0;             // visit-once steps: bytes of the holding area and of the node lists
+};
 }  // namespace
 
 struct gss_sampler {
@@ -124,6 +204,7 @@ struct gss_sampler {
   double fetch_fraction = 0.0;           // OTF_FETCH: delta
   uint64_t seed = 0;
   hipStream_t stream = nullptr;          // the caller's stream
+  HostKit* kit = nullptr;                // owns the streams, events and pinned words below
   hipEvent_t user_ready = nullptr;       // recorded on the caller's stream when it has work pending at enqueue
   hipStream_t work = nullptr;            // internal, non-blocking: every tick runs here
   gss_alloc_fn alloc = nullptr;
@@ -145,6 +226,7 @@ struct gss_sampler {
   hipStream_t fill_stream = nullptr;
   hipEvent_t fill_go = nullptr, fill_done = nullptr;
   int64_t prefetched_epoch = -1;         // epoch whose rows are (being) written into the idle set; -1: none
+  int epoch_steps = 0;                   // steps enqueued in the current epoch
   long long* stamp[GSS_MAX_RELATIONS] = {};
   int32_t theta = -1;                    // degree split: nodes with deg <= theta keep no cache row (< 0: no split)
   int32_t* row_of[GSS_MAX_RELATIONS] = {};   // degree split: node -> table row or -1
@@ -156,12 +238,14 @@ struct gss_sampler {
   bool heavy_ready = false;
   bool set_filled[MAX_TABLE_SETS] = {};
   int64_t cache_bytes = 0;               // tables + row maps + stamps
+  int32_t* states_d = nullptr;           // the device states, one allocation: create-time, fill stream, then one per slot
   int32_t* state_d = nullptr;            // create-time state (graph validation, initial fill)
   int32_t* state_h = nullptr;
   int32_t* fill_state_d = nullptr;       // error flag of the refreshes computed ahead of time on the fill stream, and its
   int32_t* fill_state_h = nullptr;       // pinned host copy (copied after every such refresh, checked when its epoch starts)
   int state_words = 0;
   Buf checksum;
+  Buf map_counts, heavy_map;             // scratch of gss_create
   bool use_direct = true;
   bool shared = false;                   // one table serves all layers (SHARED_OTF, SHARED_FCR)
   bool fcr = false;                      // every table is rewritten when floor(step/R) changes (FCR, SHARED_FCR, OTF_LAYER)
@@ -189,9 +273,9 @@ struct gss_sampler {
   // kernels stride over whatever the frontier turns out to be, so a wrong guess only costs time.
   float fill_ratio[GSS_MAX_LAYERS];
   Slot slot[GSS_MAX_IN_FLIGHT];
+  StepSizes largest;
   HopParams tick_all[2 * GSS_MAX_IN_FLIGHT], tick_launch[TICK_MAX_SLICES];   // scratch of tick(): slices of a tick, and of one launch
-  hipEvent_t tick_ev[TICK_EVENTS] = {};  // completion events of the ticks in which steps finish, used round-robin
-  int tick_ev_next = 0;
+  int tick_ev_next = 0;                  // next of the kit's completion events (for the ticks in which steps finish, used round-robin)
   int steps_per_tick = 1, unlaunched = 0; // steps enqueued since the last tick
   bool waited = false;                   // the last call collected a step: a second one in a row means that the caller is draining
   int ring = GSS_MAX_IN_FLIGHT;          // slots in use, round-robin: the most steps that may be in flight
@@ -326,9 +410,9 @@ SlotConst slot_const(const gss_sampler* s, const Slot& sl) {
   c.ht.mask = sl.hash_cap ? sl.hash_cap - 1 : 0;
   c.state = sl.state_d;
   c.state_host = sl.state_h_dev;
-  c.picks = (int32_t*)sl.picks.p; c.order = (uint32_t*)sl.order.p; c.ranks = (uint32_t*)sl.ranks.p;
-  c.partial_first = (int32_t*)sl.partial_first.p; c.partial_edge = (int32_t*)sl.partial_edge.p;
-  c.first_off = (int32_t*)sl.first_off.p; c.edge_off = (int32_t*)sl.edge_off.p;
+  c.picks = sl.picks; c.order = sl.order; c.ranks = sl.ranks;
+  c.partial_first = sl.partial_first; c.partial_edge = sl.partial_edge;
+  c.first_off = sl.first_off; c.edge_off = sl.edge_off;
   return c;
 }
 
@@ -519,7 +603,7 @@ gss_status tick(gss_sampler* s, int* issued) {
   hipEvent_t done = nullptr;
   for (int i = 0; i < n; ++i)
     if (pick[i].item >= 0 && pick[i].item + 1 == take[i]->items.num_items) {
-      if (!done) { done = s->tick_ev[s->tick_ev_next]; s->tick_ev_next = (s->tick_ev_next + 1) % TICK_EVENTS; }
+      if (!done) { done = s->kit->tick_ev[s->tick_ev_next]; s->tick_ev_next = (s->tick_ev_next + 1) % TICK_EVENTS; }
       take[i]->done = done;
     }
   s->unlaunched = 0;
@@ -560,6 +644,14 @@ gss_status drain(gss_sampler* s) {
 // the work stream has been given so far; the work stream waits for `fill_done` before it gets a step that reads
 // the set.
 gss_status fill_on_fill_stream(gss_sampler* s, uint32_t stepword, int set) {
+  if (!s->fill_stream) {
+    HostKit* k = s->kit;
+    if (!k->fill_stream && hipStreamCreateWithFlags(&k->fill_stream, hipStreamNonBlocking) != hipSuccess) {
+      k->fill_stream = nullptr;
+      return fail(s, GSS_ERR_DEVICE, "hipStreamCreateWithFlags: %s", hipGetErrorString(hipGetLastError()));
+    }
+    s->fill_stream = k->fill_stream;
+  }
   HIP_TRY(s, hipEventRecord(s->fill_go, s->work));
   HIP_TRY(s, hipStreamWaitEvent(s->fill_stream, s->fill_go, 0));
   gss_status rs = fill_all_tables(s, stepword, s->fill_state_d, s->fill_stream, set, s->cur_set);
@@ -574,6 +666,10 @@ gss_status fill_on_fill_stream(gss_sampler* s, uint32_t stepword, int set) {
 gss_status maybe_prefetch_epoch(gss_sampler* s) {
   if (!s->fcr || s->nsets < 2 || s->prefetched_epoch >= 0 || (s->epoch + 1) * s->period >= (int64_t(1) << 32))
     return GSS_OK;
+  // (not next to the first step of an epoch: the first step of a sampler would share the chip with a fill of whole tables -
+  // 2.4M nodes, three layers: that step's launches took 60-110 us each instead of 7-20 -, and a refresh needs a fraction of
+  // the time of two steps.  An epoch of one or two steps has no later one to spare.)
+  if (s->epoch_steps < std::max(1, std::min(2, s->period - 1))) return GSS_OK;
   const int idle = (s->cur_set + 1) % s->nsets;
   for (const Slot& o : s->slot)
     if (o.pending && o.table_set == idle && o.items.open()) return GSS_OK;
@@ -594,27 +690,15 @@ void destroy_impl(gss_sampler* s) {
       for (int r = 0; r < GSS_MAX_RELATIONS; ++r) { release(s, sl.src_local[t][r]); release(s, sl.dst_local[t][r]); }
       for (int q = 0; q < GSS_MAX_NODE_TYPES; ++q) release(s, sl.src_nodes[t][q]);
     }
-    Buf* bufs[] = {&sl.hash, &sl.direct, &sl.picks, &sl.order, &sl.ranks, &sl.partial_first, &sl.partial_edge,
-                   &sl.first_off, &sl.edge_off, &sl.visit, &sl.held, &sl.list, &sl.counts};
-    for (Buf* b : bufs) release(s, *b);
-    dev_free(s, sl.state_d);
-    if (sl.state_h) (void)hipHostFree(sl.state_h);
+    for (Buf* b : {&sl.hash, &sl.direct, &sl.scratch, &sl.visit, &sl.held, &sl.list, &sl.counts}) release(s, *b);
   }
   dev_free(s, s->relc_d);
   dev_free(s, s->slotc_d);
-  if (s->work) (void)hipStreamDestroy(s->work);
-  if (s->fill_stream) (void)hipStreamDestroy(s->fill_stream);
-  if (s->fill_go) (void)hipEventDestroy(s->fill_go);
-  if (s->fill_done) (void)hipEventDestroy(s->fill_done);
-  for (hipEvent_t ev : s->tick_ev) if (ev) (void)hipEventDestroy(ev);
   for (int r = 0; r < GSS_MAX_RELATIONS; ++r) { dev_free(s, s->stamp[r]); dev_free(s, s->row_of[r]); dev_free(s, s->heavy_list[r]); }
-  dev_free(s, s->state_d);
-  if (s->state_h) (void)hipHostFree(s->state_h);
-  dev_free(s, s->fill_state_d);
-  if (s->fill_state_h) (void)hipHostFree(s->fill_state_h);
-  if (s->user_ready) (void)hipEventDestroy(s->user_ready);
-  release(s, s->checksum);
+  dev_free(s, s->states_d);
+  release(s, s->checksum); release(s, s->map_counts); release(s, s->heavy_map);
   delete s->timer;
+  leave_kit(s->kit);
   delete s;
 }
 
@@ -727,13 +811,7 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
   if (tn.dedupe_layout) s->use_direct = tn.dedupe_layout == 1;
 
   s->state_words = ST_COUNTS + (GSS_MAX_LAYERS + 1) * s->T + GSS_MAX_LAYERS * s->R;
-  const size_t state_bytes = sizeof(int32_t) * (size_t)s->state_words;
-  s->state_d = (int32_t*)dev_alloc(s, state_bytes);
-  if (!s->state_d) return bail(GSS_ERR_OOM);
-  hipError_t e = hipHostMalloc((void**)&s->state_h, state_bytes, hipHostMallocDefault);
-  if (e != hipSuccess) { s->state_h = nullptr; return hipfail(e); }
-  if ((e = hipMemsetAsync(s->state_d, 0, state_bytes, s->stream)) != hipSuccess) return hipfail(e);
-  if ((e = hipEventCreateWithFlags(&s->user_ready, hipEventDisableTiming)) != hipSuccess) { s->user_ready = nullptr; return hipfail(e); }
+  hipError_t e = hipSuccess;
   // Modes whose sample phases write no table have no dependency between steps: a tick can start two of them,
   // which halves the launches and the idle time between them per step, where a launch has the slices for it
   // (one-relation graphs: the compact form carries 24).  Measured on the 1,024-seed workload: FBL and OTF fetch
@@ -763,52 +841,74 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
   // for up to three hops; six were 0.6 % slower on the 4,096-seed shared-table workload, four 8 %)
   if (s->visit_once) s->ring = std::min(GSS_MAX_IN_FLIGHT, std::max(5, s->L + 2));
   if (tn.pipeline_depth) s->ring = tn.pipeline_depth;
-  if ((e = hipStreamCreateWithFlags(&s->work, hipStreamNonBlocking)) != hipSuccess) { s->work = nullptr; return hipfail(e); }
-  for (hipEvent_t& ev : s->tick_ev)
-    if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) { ev = nullptr; return hipfail(e); }
-  if (m_fcr) {
-    if ((e = hipStreamCreateWithFlags(&s->fill_stream, hipStreamNonBlocking)) != hipSuccess) { s->fill_stream = nullptr; return hipfail(e); }
-    if ((e = hipEventCreateWithFlags(&s->fill_go, hipEventDisableTiming)) != hipSuccess) { s->fill_go = nullptr; return hipfail(e); }
-    if ((e = hipEventCreateWithFlags(&s->fill_done, hipEventDisableTiming)) != hipSuccess) { s->fill_done = nullptr; return hipfail(e); }
-    s->fill_state_d = (int32_t*)dev_alloc(s, state_bytes);
-    if (!s->fill_state_d) return bail(GSS_ERR_OOM);
-    if ((e = hipMemsetAsync(s->fill_state_d, 0, state_bytes, s->stream)) != hipSuccess) return hipfail(e);
-    if ((e = hipHostMalloc((void**)&s->fill_state_h, state_bytes, hipHostMallocDefault)) != hipSuccess) { s->fill_state_h = nullptr; return hipfail(e); }
-    memset(s->fill_state_h, 0, state_bytes);
+  // ---- device states and their pinned host copies, 256 bytes apart: create-time, fill stream, one per slot of the ring ----
+  const size_t stride = (sizeof(int32_t) * (size_t)s->state_words + 255) / 256 * 256, words = stride / sizeof(int32_t);
+  const size_t state_bytes = stride * (size_t)(s->ring + 2);
+  s->states_d = (int32_t*)dev_alloc(s, state_bytes);
+  if (!s->states_d) return bail(GSS_ERR_OOM);
+  if ((e = take_kit(state_bytes, &s->kit)) != hipSuccess) return hipfail(e);
+  s->work = s->kit->work;
+  s->user_ready = s->kit->user_ready; s->fill_go = s->kit->fill_go; s->fill_done = s->kit->fill_done;
+  memset(s->kit->pinned, 0, state_bytes);
+  int32_t* const pinned = (int32_t*)s->kit->pinned;
+  s->state_d = s->states_d; s->state_h = pinned;
+  s->fill_state_d = s->states_d + words; s->fill_state_h = pinned + words;
+  for (int i = 0; i < s->ring; ++i) {      // (the slots beyond the ring are never used)
+    Slot& sl = s->slot[i];
+    sl.state_d = s->states_d + (size_t)(i + 2) * words;
+    sl.state_h = pinned + (size_t)(i + 2) * words;
+    sl.state_h_dev = (int32_t*)s->kit->pinned_dev + (size_t)(i + 2) * words;
+    sl.out_nodes.resize((size_t)GSS_MAX_LAYERS * s->T);
+    sl.out_edges.resize((size_t)GSS_MAX_LAYERS * s->R);
   }
+  if ((e = launch_fill_i64((long long*)s->states_d, (int64_t)(state_bytes / 8), 0, s->stream)) != hipSuccess) return hipfail(e);
 
-  // The fill kernels index the adjacency through indptr: validate the graph before touching it.
-  for (int r = 0; r < s->R; ++r) {
+  // One readback answers what the set-up needs to know of the graph (every one costs a round trip to the host):
+  //  - is it valid?  (the fill kernels index the adjacency through indptr; everything before them reads indptr only)
+  //  - degree split: which nodes keep a row (deg > theta), per relation - the tables then hold only those rows;
+  //  - epoch-refreshed modes: how many rows a refresh has to recompute (nodes with a row and more than k neighbors).
+  int64_t max_n = 0;
+  for (int r = 0; r < s->R; ++r) max_n = std::max(max_n, s->num_nodes[s->rel[r].dst_type]);
+  if ((s->theta >= 0 || s->fcr) && !ensure(s, s->map_counts, sizeof(int32_t) * (size_t)(max_n / 1024 + 2))) return bail(GSS_ERR_OOM);
+  if (s->fcr && !ensure(s, s->heavy_map, sizeof(int32_t) * (size_t)std::max<int64_t>(max_n, 1))) return bail(GSS_ERR_OOM);
+  int32_t* const chunk_counts = (int32_t*)s->map_counts.p;
+  int32_t* const heavy_map = (int32_t*)s->heavy_map.p;
+  auto heavy_rows = [&](int r) {           // -> heavy_map, and the number of rows in a state word
     const gss_relation& q = s->rel[r];
-    e = launch_validate_graph(q.indptr, q.indptr_is_64, s->num_nodes[q.dst_type], q.indices, q.nnz,
-                              s->num_nodes[q.src_type], s->state_d, s->stream);
-    if (e != hipSuccess) return hipfail(e);
+    return launch_build_row_map(q.indptr, q.indptr_is_64, s->num_nodes[q.dst_type], std::max(s->k, s->theta), chunk_counts, heavy_map,
+                                s->state_d + ST_COUNTS + s->R + r, s->stream);
+  };
+  for (int r = 0; r < s->R && e == hipSuccess; ++r) {
+    const gss_relation& q = s->rel[r];
+    const int64_t n = s->num_nodes[q.dst_type];
+    e = launch_validate_graph(q.indptr, q.indptr_is_64, n, q.indices, q.nnz, s->num_nodes[q.src_type], s->state_d, s->stream);
+    s->table_rows[r] = n;
+    if (s->theta >= 0 && e == hipSuccess) {
+      s->row_of[r] = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)n);
+      if (!s->row_of[r]) return bail(GSS_ERR_OOM);
+      s->cache_bytes += (int64_t)sizeof(int32_t) * n;
+      e = launch_build_row_map(q.indptr, q.indptr_is_64, n, s->theta, chunk_counts, s->row_of[r], s->state_d + ST_COUNTS + r, s->stream);
+    }
+    if (s->fcr && n > 0 && e == hipSuccess) e = heavy_rows(r);
   }
+  if (e != hipSuccess) return hipfail(e);
   if (read_create_state(s) != GSS_OK) return bail(GSS_ERR_DEVICE);
   if (s->state_h[ST_ERROR] & ERR_GRAPH) return bail(GSS_ERR_INVALID_GRAPH);
-
-  // Degree split: number the nodes that keep a row (deg > theta), per relation; the tables then hold
-  // only those rows.  The row counts come back in the state words after the error flag.
-  for (int r = 0; r < s->R; ++r) s->table_rows[r] = s->num_nodes[s->rel[r].dst_type];
-  if (s->theta >= 0) {
-    int64_t max_n = 0;
-    for (int r = 0; r < s->R; ++r) max_n = std::max(max_n, s->num_nodes[s->rel[r].dst_type]);
-    int32_t* chunk_counts = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)(max_n / 1024 + 2));
-    if (!chunk_counts) return bail(GSS_ERR_OOM);
-    for (int r = 0; r < s->R && e == hipSuccess; ++r) {
-      const gss_relation& q = s->rel[r];
-      const int64_t n = s->num_nodes[q.dst_type];
-      s->row_of[r] = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)n);
-      if (!s->row_of[r]) { dev_free(s, chunk_counts); return bail(GSS_ERR_OOM); }
-      s->cache_bytes += (int64_t)sizeof(int32_t) * n;
-      e = launch_build_row_map(q.indptr, q.indptr_is_64, n, s->theta, chunk_counts, s->row_of[r],
-                               s->state_d + ST_COUNTS + r, s->stream);
-    }
-    const gss_status rs = (e == hipSuccess) ? read_create_state(s) : GSS_ERR_DEVICE;
-    dev_free(s, chunk_counts);     // the stream is idle after the readback
-    if (rs != GSS_OK) return bail(GSS_ERR_DEVICE);
-    for (int r = 0; r < s->R; ++r) s->table_rows[r] = s->state_h[ST_COUNTS + r];
+  for (int r = 0; r < s->R; ++r) {
+    if (s->theta >= 0) s->table_rows[r] = s->state_h[ST_COUNTS + r];
+    if (s->fcr) s->num_heavy[r] = s->state_h[ST_COUNTS + s->R + r];
   }
+  // the lists of those rows
+  for (int r = 0; r < s->R && s->fcr; ++r) {
+    if (s->num_heavy[r] <= 0) continue;
+    s->heavy_list[r] = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)s->num_heavy[r]);
+    if (!s->heavy_list[r]) return bail(GSS_ERR_OOM);
+    s->cache_bytes += (int64_t)sizeof(int32_t) * s->num_heavy[r];
+    if (s->R > 1) e = heavy_rows(r);       // (the map holds one relation at a time)
+    if (e == hipSuccess) e = launch_list_from_map(heavy_map, s->num_nodes[s->rel[r].dst_type], s->heavy_list[r], s->stream);
+    if (e != hipSuccess) return hipfail(e);
+  }
+  s->heavy_ready = s->fcr;
   // FCR: as many sets of tables as the epochs the steps in flight can span, plus the one being computed ahead
   // (a step reads its epoch's set until its last sample phase has run: with `ring` steps in flight and a refresh
   // every `period` steps that is 2 + ring / period sets, three at least, MAX_TABLE_SETS at most) - when they are
@@ -848,54 +948,20 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
     rc.is64 = s->rel[r].indptr_is_64;
     rc.n_dst = (int32_t)s->num_nodes[s->rel[r].dst_type];
   }
-  s->relc_d = (RelConst*)dev_alloc(s, sizeof(RelConst) * GSS_MAX_RELATIONS);
-  if (!s->relc_d) return bail(GSS_ERR_OOM);
-  if ((e = hipMemcpyAsync(s->relc_d, s->relc_h, sizeof(RelConst) * GSS_MAX_RELATIONS, hipMemcpyHostToDevice, s->stream)) != hipSuccess)
-    return hipfail(e);
-  s->slotc_d = (SlotConst*)dev_alloc(s, sizeof(SlotConst) * GSS_MAX_IN_FLIGHT);
+  if (s->R > 2 || s->T > 2) {              // (smaller graphs carry them in the kernel arguments)
+    s->relc_d = (RelConst*)dev_alloc(s, sizeof(RelConst) * GSS_MAX_RELATIONS);
+    if (!s->relc_d) return bail(GSS_ERR_OOM);
+    if ((e = hipMemcpyAsync(s->relc_d, s->relc_h, sizeof(RelConst) * GSS_MAX_RELATIONS, hipMemcpyHostToDevice, s->stream)) != hipSuccess)
+      return hipfail(e);
+  }
+  s->slotc_d = (SlotConst*)dev_alloc(s, sizeof(SlotConst) * GSS_MAX_IN_FLIGHT);   // (an entry is written when its slot's buffers grow)
   if (!s->slotc_d) return bail(GSS_ERR_OOM);
-  if ((e = hipMemsetAsync(s->slotc_d, 0, sizeof(SlotConst) * GSS_MAX_IN_FLIGHT, s->stream)) != hipSuccess) return hipfail(e);
   if (!ensure(s, s->checksum, 8)) return bail(GSS_ERR_OOM);
-  for (int i = 0; i < s->ring; ++i) {      // (the slots beyond the ring are never used)
-    Slot& sl = s->slot[i];
-    sl.state_d = (int32_t*)dev_alloc(s, state_bytes);
-    if (!sl.state_d) return bail(GSS_ERR_OOM);
-    if ((e = hipMemsetAsync(sl.state_d, 0, state_bytes, s->stream)) != hipSuccess) return hipfail(e);
-    e = hipHostMalloc((void**)&sl.state_h, state_bytes, hipHostMallocDefault);
-    if (e != hipSuccess) { sl.state_h = nullptr; return hipfail(e); }
-    if ((e = hipHostGetDevicePointer((void**)&sl.state_h_dev, sl.state_h, 0)) != hipSuccess) return hipfail(e);
-    sl.out_nodes.resize((size_t)GSS_MAX_LAYERS * s->T);
-    sl.out_edges.resize((size_t)GSS_MAX_LAYERS * s->R);
-  }
-  if (s->fcr) {   // the list of rows a refresh has to recompute (nodes with a row and more than k neighbors)
-    int64_t max_n = 0;
-    for (int r = 0; r < s->R; ++r) max_n = std::max(max_n, s->num_nodes[s->rel[r].dst_type]);
-    int32_t* chunk_counts = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)(max_n / 1024 + 2));
-    int32_t* map = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)std::max<int64_t>(max_n, 1));
-    gss_status hs = (chunk_counts && map) ? GSS_OK : GSS_ERR_OOM;
-    for (int r = 0; r < s->R && hs == GSS_OK; ++r) {
-      const gss_relation& q = s->rel[r];
-      const int64_t n = s->num_nodes[q.dst_type];
-      if (n <= 0) continue;
-      e = launch_build_row_map(q.indptr, q.indptr_is_64, n, std::max(s->k, s->theta), chunk_counts, map,
-                               s->state_d + ST_COUNTS, s->stream);
-      if (e != hipSuccess || read_create_state(s) != GSS_OK) { hs = GSS_ERR_DEVICE; break; }
-      s->num_heavy[r] = s->state_h[ST_COUNTS];
-      if (s->num_heavy[r] > 0) {
-        s->heavy_list[r] = (int32_t*)dev_alloc(s, sizeof(int32_t) * (size_t)s->num_heavy[r]);
-        if (!s->heavy_list[r]) { hs = GSS_ERR_OOM; break; }
-        s->cache_bytes += (int64_t)sizeof(int32_t) * s->num_heavy[r];
-        if (launch_list_from_map(map, n, s->heavy_list[r], s->stream) != hipSuccess ||
-            hipStreamSynchronize(s->stream) != hipSuccess) { hs = GSS_ERR_DEVICE; break; }
-      }
-    }
-    dev_free(s, chunk_counts);
-    dev_free(s, map);
-    if (hs != GSS_OK) return bail(hs);
-    s->heavy_ready = true;
-  }
-  if (fill_all_tables(s, 0, s->state_d, s->stream) != GSS_OK) return bail(GSS_ERR_DEVICE);
-  if (read_create_state(s) != GSS_OK) return bail(GSS_ERR_DEVICE);
+  const gss_status filled = fill_all_tables(s, 0, s->state_d, s->stream);
+  const gss_status read = filled == GSS_OK ? read_create_state(s) : filled;
+  if (read != GSS_OK) return bail(GSS_ERR_DEVICE);
+  release(s, s->map_counts);             // (the stream is idle)
+  release(s, s->heavy_map);
   if (s->state_h[ST_ERROR] != 0) return bail(GSS_ERR_INVALID_GRAPH);   // e.g. repeated neighbor ids in a row
   *out = s;
   return GSS_OK;
@@ -906,70 +972,88 @@ gss_status gss_destroy(gss_sampler* s) {
   return GSS_OK;
 }
 
-// Makes the buffers of slot `sl` large enough for a step planned like `plan` (L hops, max_slots pick slots, max_keys
-// dedupe keys), clears a new dedupe table on `st`, and brings the slot's entry of the device table up to date.
-static gss_status grow_slot(gss_sampler* s, Slot& sl, const Slot& plan, int L, int64_t max_slots, int64_t max_keys,
-                            hipStream_t st, bool* grew) {
+// Takes the sizes of a step's plan (L hops, max_slots pick slots, max_keys dedupe keys) into `g`.
+static void note_sizes(const gss_sampler* s, const Slot& plan, int L, int64_t max_slots, int64_t max_keys, StepSizes& g) {
+  g.L = std::max(g.L, L);
+  for (int h = 0; h < L; ++h) {
+    const int l = L - 1 - h;
+    for (int t = 0; t < s->T; ++t) g.src[l][t] = std::max(g.src[l][t], plan.fub[h + 1][t]);
+    for (int r = 0; r < s->R; ++r) g.edges[l][r] = std::max(g.edges[l][r], plan.slots_ub[h][r]);
+  }
+  g.slots = std::max(g.slots, max_slots);
+  g.keys = std::max(g.keys, max_keys);
+  if (plan.chain) {
+    const ChainArgs& C = plan.chain_args;
+    size_t entries = 0;
+    for (int h = 1; h < L; ++h) entries = (size_t)C.loff[h] + (size_t)CHAIN_SEGS * C.lcap[h];
+    g.held = std::max(g.held, sizeof(int32_t) * ((size_t)C.off[L - 1] + (size_t)C.V[L - 1] * C.f(L - 1)));
+    g.list = std::max(g.list, sizeof(uint64_t) * entries);
+  }
+}
+
+// Makes the buffers of slot `sl` large enough for steps of size `g`, clears a new dedupe table on `st`, and
+// brings the slot's entry of the device table up to date.  A slot grows when a step is about to use it, not before: the
+// first step of a sampler pays for one slot, a caller of blocking steps spreads the rest over its first steps.
+static gss_status grow_slot(gss_sampler* s, Slot& sl, const StepSizes& g, bool chain, hipStream_t st) {
   const int T = s->T, R = s->R;
-  bool any = false;
-  auto need = [&](Buf& b, size_t bytes) { if (b.bytes >= bytes && b.p) return true; any = true; return ensure(s, b, bytes); };
   if (s->use_direct && !sl.direct.p) {
-    if (!need(sl.direct, sizeof(uint64_t) * (size_t)std::max<int64_t>(s->total_nodes, 1)))
+    if (!ensure(s, sl.direct, sizeof(uint64_t) * (size_t)std::max<int64_t>(s->total_nodes, 1)))
       return fail(s, GSS_ERR_OOM, "step: dedupe table allocation failed");
-    HIP_TRY(s, hipMemsetAsync(sl.direct.p, 0xFF, sl.direct.bytes, st));
+    HIP_TRY(s, launch_fill_i64((long long*)sl.direct.p, (int64_t)(sl.direct.bytes / 8), -1, st));
     sl.ver = s->first_version;
   }
   if (!s->use_direct) {
     uint64_t cap = 1024;
-    while (cap < 2 * (uint64_t)max_keys) cap <<= 1;
+    while (cap < 2 * (uint64_t)g.keys) cap <<= 1;
     if (sl.hash.bytes < cap * sizeof(HashEntry)) {
-      if (!need(sl.hash, cap * sizeof(HashEntry))) return fail(s, GSS_ERR_OOM, "step: dedupe table allocation failed");
-      HIP_TRY(s, hipMemsetAsync(sl.hash.p, 0xFF, sl.hash.bytes, st));
+      if (!ensure(s, sl.hash, cap * sizeof(HashEntry))) return fail(s, GSS_ERR_OOM, "step: dedupe table allocation failed");
+      HIP_TRY(s, launch_fill_i64((long long*)sl.hash.p, (int64_t)(sl.hash.bytes / 8), -1, st));
       sl.ver = s->first_version;
     }
   }
   sl.hash_cap = s->use_direct ? 0 : sl.hash.bytes / sizeof(HashEntry);   // power of two by construction
-  const size_t slot_bytes = sizeof(int32_t) * (size_t)std::max<int64_t>(max_slots, 1);
-  const size_t tile_bytes = sizeof(int32_t) * (size_t)std::max<int64_t>(max_slots / TILE, 1);
-  if (!need(sl.picks, slot_bytes) || !need(sl.order, slot_bytes) || !need(sl.ranks, slot_bytes) ||
-      !need(sl.partial_first, tile_bytes) || !need(sl.partial_edge, tile_bytes) ||
-      !need(sl.first_off, tile_bytes) || !need(sl.edge_off, tile_bytes))
-    return fail(s, GSS_ERR_OOM, "step: scratch allocation failed");
-  for (int h = 0; h < L; ++h) {
-    const int l = L - 1 - h;
+  // what the phases hand to each other: pick slots (whole tiles), then the tile totals, one allocation
+  const size_t slots = (size_t)std::max<int64_t>(g.slots, 1), tiles = (std::max<size_t>(slots / TILE, 1) + 63) / 64 * 64;
+  const size_t scratch = sizeof(int32_t) * (3 * slots + 4 * tiles);
+  if (sl.scratch.bytes < scratch || !sl.scratch.p) {
+    if (!ensure(s, sl.scratch, scratch)) return fail(s, GSS_ERR_OOM, "step: scratch allocation failed");
+    int32_t* q = (int32_t*)sl.scratch.p;
+    sl.picks = q; q += slots;
+    sl.order = (uint32_t*)q; q += slots;
+    sl.ranks = (uint32_t*)q; q += slots;
+    sl.partial_first = q; q += tiles;
+    sl.partial_edge = q; q += tiles;
+    sl.first_off = q; q += tiles;
+    sl.edge_off = q;
+  }
+  auto out = [&](Buf& b, int64_t n) { return ensure(s, b, sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1)); };
+  for (int l = 0; l < g.L; ++l) {
     for (int t = 0; t < T; ++t)
-      if (!need(sl.src_nodes[l][t], sizeof(int32_t) * (size_t)std::max<int64_t>(plan.fub[h + 1][t], 1)))
-        return fail(s, GSS_ERR_OOM, "step: output allocation failed");
+      if (!out(sl.src_nodes[l][t], g.src[l][t])) return fail(s, GSS_ERR_OOM, "step: output allocation failed");
     for (int r = 0; r < R; ++r)
-      if (!need(sl.src_local[l][r], sizeof(int32_t) * (size_t)std::max<int64_t>(plan.slots_ub[h][r], 1)) ||
-          !need(sl.dst_local[l][r], sizeof(int32_t) * (size_t)std::max<int64_t>(plan.slots_ub[h][r], 1)))
+      if (!out(sl.src_local[l][r], g.edges[l][r]) || !out(sl.dst_local[l][r], g.edges[l][r]))
         return fail(s, GSS_ERR_OOM, "step: output allocation failed");
   }
-  if (plan.chain) {
-    const ChainArgs& C = plan.chain_args;
+  if (chain) {
     if (!sl.visit.p) {
-      if (!need(sl.visit, sizeof(uint64_t) * (size_t)std::max<int64_t>(s->total_nodes, 1)))
+      if (!ensure(s, sl.visit, sizeof(uint64_t) * (size_t)std::max<int64_t>(s->total_nodes, 1)))
         return fail(s, GSS_ERR_OOM, "step: visit table allocation failed");
-      HIP_TRY(s, hipMemsetAsync(sl.visit.p, 0xFF, sl.visit.bytes, st));
+      HIP_TRY(s, launch_fill_i64((long long*)sl.visit.p, (int64_t)(sl.visit.bytes / 8), -1, st));
     }
-    const size_t held = (size_t)C.off[L - 1] + (size_t)C.V[L - 1] * C.f(L - 1);
-    if (!need(sl.held, sizeof(int32_t) * std::max<size_t>(held, 1))) return fail(s, GSS_ERR_OOM, "step: holding area allocation failed");
-    size_t entries = 0;
-    for (int h = 1; h < L; ++h) entries = (size_t)C.loff[h] + (size_t)CHAIN_SEGS * C.lcap[h];
-    if (!need(sl.list, sizeof(uint64_t) * std::max<size_t>(entries, 1))) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
+    if (!ensure(s, sl.held, g.held)) return fail(s, GSS_ERR_OOM, "step: holding area allocation failed");
+    if (!ensure(s, sl.list, g.list)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
     if (!sl.counts.p) {
-      if (!need(sl.counts, sizeof(uint32_t) * 2 * CHAIN_MAX_HOPS * CHAIN_SEGS * CHAIN_COUNT_STRIDE)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
-      HIP_TRY(s, hipMemsetAsync(sl.counts.p, 0, sl.counts.bytes, st));
+      if (!ensure(s, sl.counts, sizeof(uint32_t) * 2 * CHAIN_MAX_HOPS * CHAIN_SEGS * CHAIN_COUNT_STRIDE)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
+      HIP_TRY(s, launch_fill_i64((long long*)sl.counts.p, (int64_t)(sl.counts.bytes / 8), 0, st));
     }
   }
-  // the slot's entry of the device table follows its buffers (they only change while they grow)
+  // the slot's entry of the device table follows its buffers (only the compact launches, of more than 12 slices, read it)
   const int idx = (int)(&sl - s->slot);
   const SlotConst sc = slot_const(s, sl);
-  if (memcmp(&sc, &s->slotc_h[idx], sizeof sc) != 0) {
+  if (s->tick_cap > 12 && memcmp(&sc, &s->slotc_h[idx], sizeof sc) != 0) {
     s->slotc_h[idx] = sc;
-    HIP_TRY(s, hipMemcpyAsync(s->slotc_d + idx, &s->slotc_h[idx], sizeof sc, hipMemcpyHostToDevice, st));
+    HIP_TRY(s, launch_store_slot(s->slotc_d + idx, sc, st));
   }
-  if (grew) *grew = any;
   return GSS_OK;
 }
 
@@ -1072,23 +1156,14 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     HIP_TRY(s, hipStreamWaitEvent(st, s->user_ready, 0));
   }
 
-  // ---- buffers (grow-only) of this slot - and, with the same sizes, of every slot of the ring that has not held a
-  //      step yet: the allocations of a run then all happen at its first step, not once per slot as the ring is first
-  //      walked.  (A slot that has held a step keeps its buffers until it is used again: the caller may still be
-  //      reading that step's blocks.) ----
+  // ---- buffers (grow-only) of this slot ----
   sl.chain = chain;
   sl.chain_args = chain_args;
-  {
-    bool grew = false;
-    gss_status gs = grow_slot(s, sl, sl, L, max_slots, max_keys, st, &grew);
-    if (gs != GSS_OK) return gs;
-    if (grew)
-      for (int q = 0; q < s->ring; ++q) {
-        Slot& o = s->slot[q];
-        if (&o == &sl || o.pending || o.used) continue;
-        if ((gs = grow_slot(s, o, sl, L, max_slots, max_keys, st, nullptr)) != GSS_OK) return gs;
-      }
-  }
+  StepSizes sizes = s->largest;
+  note_sizes(s, sl, L, max_slots, max_keys, sizes);
+  gss_status gs = grow_slot(s, sl, sizes, chain, st);
+  if (gs != GSS_OK) return gs;
+  s->largest = sizes;                    // (a step that does not fit leaves no trace)
   if (chain) {
     sl.chain_args.held = (int32_t*)sl.held.p;
     sl.chain_args.visit = (uint64_t*)sl.visit.p;
@@ -1098,9 +1173,9 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     sl.chain_parity ^= 1;
   }
   if (sl.ver + (uint32_t)L >= VERSION_LAST) {        // version space exhausted: start over with a clean table
-    if (s->use_direct) HIP_TRY(s, hipMemsetAsync(sl.direct.p, 0xFF, sl.direct.bytes, st));
-    else HIP_TRY(s, hipMemsetAsync(sl.hash.p, 0xFF, sl.hash.bytes, st));
-    if (sl.visit.p) HIP_TRY(s, hipMemsetAsync(sl.visit.p, 0xFF, sl.visit.bytes, st));
+    if (s->use_direct) HIP_TRY(s, launch_fill_i64((long long*)sl.direct.p, (int64_t)(sl.direct.bytes / 8), -1, st));
+    else HIP_TRY(s, launch_fill_i64((long long*)sl.hash.p, (int64_t)(sl.hash.bytes / 8), -1, st));
+    if (sl.visit.p) HIP_TRY(s, launch_fill_i64((long long*)sl.visit.p, (int64_t)(sl.visit.bytes / 8), -1, st));
     sl.ver = VERSION_FIRST;
   }
   s->last_step = step;
@@ -1159,10 +1234,11 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     s->prefetched_epoch = -1;
     s->cur_set = fill_set;
     s->epoch = epoch;
+    s->epoch_steps = 0;
   }
+  if (s->epoch_steps < 2) ++s->epoch_steps;
   sl.table_set = s->cur_set;
   sl.pending = true;
-  sl.used = true;
   s->waited = false;
   s->enq = (s->enq + 1) % s->ring;
   // (two steps share a tick only while their launches are small: from about 400k expected picks per step on, a

@@ -276,6 +276,7 @@ hipError_t launch_cache_checksum_static(const int32_t* table, const int32_t* row
 // `chunk_counts` is scratch of ceil(n / 1024) + 1 words.
 hipError_t launch_build_row_map(const void* indptr, int is64, int64_t n, int32_t theta, int32_t* chunk_counts,
                                 int32_t* row_of, int32_t* num_rows, hipStream_t st);
+hipError_t launch_store_slot(SlotConst* at, const SlotConst& value, hipStream_t st);   // *at = value, without a copy command
 hipError_t launch_fill_i64(long long* p, int64_t n, long long value, hipStream_t st);
 hipError_t launch_gather_rows(const void* table, int64_t num_rows, int64_t row_bytes, const int32_t* ids, int64_t num_ids,
                               void* out, hipStream_t st);

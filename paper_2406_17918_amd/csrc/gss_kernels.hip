@@ -1657,6 +1657,10 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const VEC* __restrict_
   }
 }
 
+__global__ void store_slot_kernel(SlotConst* at, SlotConst value) {
+  if (threadIdx.x == 0) *at = value;
+}
+
 __global__ void fill_i64_kernel(long long* p, int64_t n, long long value) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = value;
 }
@@ -1929,6 +1933,11 @@ hipError_t launch_gather_rows(const void* table, int64_t num_rows, int64_t row_b
   if (align % 8 == 0) return launch_gather_t<uint2>(table, num_rows, row_bytes, ids, num_ids, out, st);
   if (align % 4 == 0) return launch_gather_t<uint32_t>(table, num_rows, row_bytes, ids, num_ids, out, st);
   return launch_gather_t<uint8_t>(table, num_rows, row_bytes, ids, num_ids, out, st);
+}
+
+hipError_t launch_store_slot(SlotConst* at, const SlotConst& value, hipStream_t st) {
+  hipLaunchKernelGGL(store_slot_kernel, dim3(1), dim3(64), 0, st, at, value);
+  return hipGetLastError();
 }
 
 hipError_t launch_fill_i64(long long* p, int64_t n, long long value, hipStream_t st) {
