@@ -168,7 +168,7 @@ typedef struct {
   int32_t steps_per_tick;       /* 1 | 2: steps a launch starts (2 only in modes that never write a table)           */
   int32_t insert_phase;         /* 1: every hop gets a separate insert phase (visit-once steps: after the place phase,
                                    which they otherwise never get), 2: none does                                      */
-  int32_t scan_phase;           /* 1: every hop gets a separate scan phase                                           */
+  int32_t scan_phase;           /* 0 | 1: accepted, no effect (tile totals are no longer scanned in a phase of their own) */
   int32_t tick_build;           /* 1: every launch uses the step kernel's 8-workgroups-per-CU build, 2: none does     */
   uint32_t first_dedupe_version;/* start of each slot's dedupe-table version counter (tests of the wrap-around)       */
   int32_t visit_once;           /* SHARED_OTF on a graph with one relation.  Default: the steps of gss_step_async run as

@@ -4,7 +4,7 @@
 // (`state`), launches are sized by host-known upper bounds with early exit, and the counts plus the
 // error flag arrive in pinned host memory, written by the step's last kernel.
 //
-// A step is a chain of phases - per hop: sample, (insert,) mark, (scan,) emit - each a latency-bound pass
+// A step is a chain of phases - per hop: sample, (insert,) mark, emit - each a latency-bound pass
 // that leaves most of the chip idle.  So the steps in flight (up to gss_pipeline_depth(), each in its own
 // "slot": device state, scratch, dedupe table, output buffers) are software-pipelined through ONE launch
 // per enqueued step, a "tick": the tick carries the next phase of every step in flight that
@@ -42,6 +42,7 @@ constexpr int64_t INSERT_SPLIT_SLOTS = 48 * 1024;   // expected pick slots of a 
 constexpr int64_t TWO_STEP_PICKS = 400 * 1024;    // expected picks of a step up to which two steps share a tick
 constexpr int64_t NARROW_MIN_NODES = 16 * 1024;     // expected frontier nodes of a launch's sample slices from which they take narrow groups
 constexpr int64_t INSERT_SMALL_SLOTS = 16 * 1024;   // ... and up to which they do, too (narrow hops)
+constexpr double SETTLE_TYPED_TILES = 256.0;        // several relations: expected tiles of a hop up to which a blocking step settles it in one launch
 constexpr int DENSE_TICK_WGS = 5000;                // workgroups of a launch from which the kernel's eight-per-CU build is used
 static_assert(GSS_MAX_LAYERS <= SCHED_MAX_LAYERS, "the phase list of a step holds GSS_MAX_LAYERS hops");
 
@@ -158,8 +159,11 @@ struct Slot {
   int32_t* state_h = nullptr;            // pinned copy of the device state, written by the last emit phase
   int32_t* state_h_dev = nullptr;        // the same memory as the device sees it
   Buf hash, direct, scratch;             // dedupe table (either layout); what the phases of a step hand to each other:
-  int32_t *picks = nullptr, *partial_first = nullptr, *partial_edge = nullptr, *first_off = nullptr, *edge_off = nullptr;
-  uint32_t *order = nullptr, *ranks = nullptr;   // ... parts of `scratch`
+  int32_t* picks = nullptr;              // ... parts of `scratch`
+  uint64_t *agg = nullptr, *recs = nullptr, *pref = nullptr;   // hand-off words (agg is the first of handoff_words)
+  uint32_t *order = nullptr, *done_counts = nullptr, *tile_sums = nullptr, *ranks = nullptr;
+  uint2* tile_off = nullptr;
+  size_t handoff_words = 0;
   Buf visit, held, list, counts;         // visit-once steps: visit table (8 bytes per node), holding area, node lists and their counters
   int chain_parity = 0;                  // which of the two counter sets the slot's next visit-once step uses
   uint32_t ver = VERSION_FIRST;          // next unused dedupe table version
@@ -251,7 +255,6 @@ struct gss_sampler {
   bool fcr = false;                      // every table is rewritten when floor(step/R) changes (FCR, SHARED_FCR, OTF_LAYER)
   bool layer_partial = false;            // ... by a partial refresh of every row instead of a fill (OTF_LAYER)
   bool otf = false;                      // partial refresh per visit (OTF, SHARED_OTF)
-  bool force_scan_kernel = false;        // gss_tuning.scan_phase: always use the separate scan phase
   int insert_policy = 0;                 // gss_tuning.insert_phase - 0: large and narrow hops get an insert phase; 1: all hops, 2: none
   int dense_policy = 0;                  // gss_tuning.tick_build - 0: launches of DENSE_TICK_WGS workgroups and more use the dense build; 1: all, 2: none
   uint32_t first_version = VERSION_FIRST;   // where a slot's dedupe-table version counter starts
@@ -397,10 +400,6 @@ Slot* oldest_pending(gss_sampler* s) {
   return nullptr;
 }
 
-bool scans_in_emit(const gss_sampler* s, const Slot& sl, int h) {
-  return sl.total_slots[h] / TILE <= EMIT_SCAN_MAX_TILES && !s->force_scan_kernel;
-}
-
 // The scratch pointers that all phases of the step held by `sl` share.
 SlotConst slot_const(const gss_sampler* s, const Slot& sl) {
   SlotConst c;
@@ -410,9 +409,7 @@ SlotConst slot_const(const gss_sampler* s, const Slot& sl) {
   c.ht.mask = sl.hash_cap ? sl.hash_cap - 1 : 0;
   c.state = sl.state_d;
   c.state_host = sl.state_h_dev;
-  c.picks = sl.picks; c.order = sl.order; c.ranks = sl.ranks;
-  c.partial_first = sl.partial_first; c.partial_edge = sl.partial_edge;
-  c.first_off = sl.first_off; c.edge_off = sl.edge_off;
+  c.picks = sl.picks; c.agg = sl.agg; c.recs = sl.recs; c.pref = sl.pref; c.tile_sums = sl.tile_sums; c.ranks = sl.ranks; c.order = sl.order; c.tile_off = sl.tile_off; c.done = sl.done_counts;
   return c;
 }
 
@@ -427,7 +424,7 @@ void fill_slice(gss_sampler* s, Slot& sl, int it, HopParams& P, int width) {
   P.band_offset = 0;
   for (int q = 0; q < l; ++q) P.band_offset += sl.fanouts[q];
   P.num_tiles_ub = (int32_t)(sl.total_slots[h] / TILE);
-  P.scan_in_emit = scans_in_emit(s, sl, h) ? 1 : 0;
+  P.f_mul = (1u << 20) / (uint32_t)P.f + 1u;
   // bit 0: the hop has an insert phase; bit 1: insert and place phases dedupe their tile in LDS first
   P.insert_split = (int32_t)((sl.insert_hops >> h) & 1u) | (s->lds_stage ? 2 : 0);
   P.edge_count_off = (GSS_MAX_LAYERS + 1) * T;
@@ -443,9 +440,9 @@ void fill_slice(gss_sampler* s, Slot& sl, int it, HopParams& P, int width) {
   P.state = sc.state;
   P.state_host = (h == L - 1) ? sc.state_host : nullptr;
   P.state_words = s->state_words;
-  P.picks = sc.picks; P.order = sc.order; P.ranks = sc.ranks;
-  P.partial_first = sc.partial_first; P.partial_edge = sc.partial_edge;
-  P.first_off = sc.first_off; P.edge_off = sc.edge_off;
+  P.picks = sc.picks; P.order = sc.order; P.tile_off = sc.tile_off;
+  if (P.phase == PH_SETTLE) { P.agg = sc.agg; P.recs = sc.recs; P.pref = sc.pref; }
+  else { P.tile_sums = sc.tile_sums; P.ranks = sc.ranks; P.done = sc.done; }
   P.slot = (int32_t)(&sl - s->slot);
   if (sl.chain) {               // visit-once step: the place phase reads the hop's picks from the holding area
     if (P.phase == PH_PLACE) {
@@ -493,9 +490,7 @@ void fill_slice(gss_sampler* s, Slot& sl, int it, HopParams& P, int width) {
     P.gx = (int32_t)std::min<int64_t>(std::max<int64_t>((want + gpw * per - 1) / (gpw * per), 1), cap);
     P.gy = R;                                    // per relation: a group per frontier node
     P.gxd = (int32_t)((P.gx * gpw + 255) / 256); P.gyd = T;   // per node type: a thread per frontier node
-  } else if (P.phase == PH_SCAN) {
-    P.gx = 1; P.gy = 1;
-  } else {                                     // insert, place, mark, emit: tiles
+  } else {                                     // insert, place, mark, emit, settle: tiles
     const int64_t tiles = (int64_t)(expect * (double)P.num_tiles_ub) + R;
     // (one workgroup per expected live tile, also on very large hops: with a cap of 1,024 workgroups, each walking
     // over several tiles, steps of 65,536 seeds were 7 % slower, of 262,144 seeds 11 %.  On graphs with several
@@ -503,8 +498,6 @@ void fill_slice(gss_sampler* s, Slot& sl, int it, HopParams& P, int width) {
     // workload is 2 % faster with it)
     const int64_t tile_cap = R > 1 ? 1024 : 16384;
     int64_t gx = std::min<int64_t>(std::max<int64_t>(std::min<int64_t>(tiles, P.num_tiles_ub), 1), tile_cap);
-    // an emit workgroup that scans in LDS keeps the edge offsets of its own tiles there
-    if (P.scan_in_emit) gx = std::max<int64_t>(gx, (P.num_tiles_ub + EMIT_OWN_TILES - 1) / EMIT_OWN_TILES);
     P.gx = (int32_t)gx;
     P.gy = 1;
     if (P.phase == PH_PLACE) {                 // ... and a row of workgroups with a thread per dst node
@@ -789,7 +782,6 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
     return bail(GSS_ERR_DEVICE);
   };
 
-  s->force_scan_kernel = tn.scan_phase == 1;
   s->insert_policy = tn.insert_phase;
   s->dense_policy = tn.tick_build;
   s->first_version = tn.first_dedupe_version ? tn.first_dedupe_version : VERSION_FIRST;
@@ -1014,17 +1006,23 @@ static gss_status grow_slot(gss_sampler* s, Slot& sl, const StepSizes& g, bool c
   sl.hash_cap = s->use_direct ? 0 : sl.hash.bytes / sizeof(HashEntry);   // power of two by construction
   // what the phases hand to each other: pick slots (whole tiles), then the tile totals, one allocation
   const size_t slots = (size_t)std::max<int64_t>(g.slots, 1), tiles = (std::max<size_t>(slots / TILE, 1) + 63) / 64 * 64;
-  const size_t scratch = sizeof(int32_t) * (3 * slots + 4 * tiles);
+  const size_t recs = (slots / 16 + 63) / 64 * 64, blocks = tiles / LOOKBACK_BLOCK * (size_t)(R + T);
+  const size_t done = COUNT_STRIDE * (DONE_WAYS + 1) / 2, words = tiles + recs + blocks + done;
+  const size_t scratch = sizeof(uint64_t) * (words + tiles) + sizeof(int32_t) * (2 * slots + recs + tiles);
   if (sl.scratch.bytes < scratch || !sl.scratch.p) {
     if (!ensure(s, sl.scratch, scratch)) return fail(s, GSS_ERR_OOM, "step: scratch allocation failed");
-    int32_t* q = (int32_t*)sl.scratch.p;
-    sl.picks = q; q += slots;
-    sl.order = (uint32_t*)q; q += slots;
-    sl.ranks = (uint32_t*)q; q += slots;
-    sl.partial_first = q; q += tiles;
-    sl.partial_edge = q; q += tiles;
-    sl.first_off = q; q += tiles;
-    sl.edge_off = q;
+    uint64_t* q = (uint64_t*)sl.scratch.p;
+    sl.agg = q; q += tiles;
+    sl.recs = q; q += recs;
+    sl.pref = q; q += blocks;
+    sl.done_counts = (uint32_t*)q; q += done;
+    sl.tile_off = (uint2*)q; q += tiles;
+    sl.picks = (int32_t*)q;
+    sl.order = (uint32_t*)(sl.picks + slots);
+    sl.ranks = sl.order + slots;
+    sl.tile_sums = sl.ranks + recs;
+    sl.handoff_words = words;
+    HIP_TRY(s, launch_fill_i64((long long*)sl.agg, (int64_t)sl.handoff_words, 0, st));
   }
   auto out = [&](Buf& b, int64_t n) { return ensure(s, b, sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1)); };
   for (int l = 0; l < g.L; ++l) {
@@ -1043,7 +1041,7 @@ static gss_status grow_slot(gss_sampler* s, Slot& sl, const StepSizes& g, bool c
     if (!ensure(s, sl.held, g.held)) return fail(s, GSS_ERR_OOM, "step: holding area allocation failed");
     if (!ensure(s, sl.list, g.list)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
     if (!sl.counts.p) {
-      if (!ensure(s, sl.counts, sizeof(uint32_t) * 2 * CHAIN_MAX_HOPS * CHAIN_SEGS * CHAIN_COUNT_STRIDE)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
+      if (!ensure(s, sl.counts, sizeof(uint32_t) * 2 * CHAIN_MAX_HOPS * CHAIN_SEGS * COUNT_STRIDE)) return fail(s, GSS_ERR_OOM, "step: node list allocation failed");
       HIP_TRY(s, launch_fill_i64((long long*)sl.counts.p, (int64_t)(sl.counts.bytes / 8), 0, st));
     }
   }
@@ -1168,15 +1166,21 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     sl.chain_args.held = (int32_t*)sl.held.p;
     sl.chain_args.visit = (uint64_t*)sl.visit.p;
     sl.chain_args.list = (uint64_t*)sl.list.p;
-    sl.chain_args.counts = (uint32_t*)sl.counts.p + sl.chain_parity * CHAIN_MAX_HOPS * CHAIN_SEGS * CHAIN_COUNT_STRIDE;
-    sl.chain_args.counts_next = (uint32_t*)sl.counts.p + (1 - sl.chain_parity) * CHAIN_MAX_HOPS * CHAIN_SEGS * CHAIN_COUNT_STRIDE;
+    sl.chain_args.counts = (uint32_t*)sl.counts.p + sl.chain_parity * CHAIN_MAX_HOPS * CHAIN_SEGS * COUNT_STRIDE;
+    sl.chain_args.counts_next = (uint32_t*)sl.counts.p + (1 - sl.chain_parity) * CHAIN_MAX_HOPS * CHAIN_SEGS * COUNT_STRIDE;
     sl.chain_parity ^= 1;
   }
   if (sl.ver + (uint32_t)L >= VERSION_LAST) {        // version space exhausted: start over with a clean table
     if (s->use_direct) HIP_TRY(s, launch_fill_i64((long long*)sl.direct.p, (int64_t)(sl.direct.bytes / 8), -1, st));
     else HIP_TRY(s, launch_fill_i64((long long*)sl.hash.p, (int64_t)(sl.hash.bytes / 8), -1, st));
     if (sl.visit.p) HIP_TRY(s, launch_fill_i64((long long*)sl.visit.p, (int64_t)(sl.visit.bytes / 8), -1, st));
+    HIP_TRY(s, launch_fill_i64((long long*)sl.agg, (int64_t)sl.handoff_words, 0, st));
     sl.ver = VERSION_FIRST;
+  } else if (((sl.ver + (uint32_t)L) & 0x1FFFFu) < (uint32_t)L + 1u) {
+    // the hand-off words of the settle phase tell versions apart by their low 17 bits: all hops of a step lie between two
+    // clearings (every 40,000 steps or so), and the tag 0 of a cleared word is never used
+    HIP_TRY(s, launch_fill_i64((long long*)sl.agg, (int64_t)sl.handoff_words, 0, st));
+    sl.ver = ((sl.ver + (uint32_t)L) & ~0x1FFFFu) + 1u;
   }
   s->last_step = step;
   sl.L = L; sl.num_seeds = num_seeds; sl.seed_type = seed_type; sl.seeds = seeds; sl.step = step;
@@ -1184,8 +1188,6 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
   sl.refresh_now = s->otf && s->n_new > 0 && (step % s->period == 0);
   sl.ver0 = sl.ver;
   sl.ver += (uint32_t)L;
-  uint32_t scan_hops = 0;                // hops whose emit phase does not scan the tile totals itself
-  for (int h = 0; h < L; ++h) scan_hops |= scans_in_emit(s, sl, h) ? 0u : (1u << h);
   // The dedupe table inserts of a hop run as a phase of their own
   //   - on wide hops (INSERT_SPLIT_SLOTS expected picks and more) of the modes without a refresh in the sample phase:
   //     there the inserts are most of the phase; with a refresh they are a small part of it and the extra pass over
@@ -1197,7 +1199,6 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
   //   as long as a tick still fits one launch.
   sl.insert_hops = 0;
   int phases = 3 * L;
-  for (int h = 0; h < L; ++h) phases += scans_in_emit(s, sl, h) ? 0 : 1;
   for (int h = L - 1; h >= 0; --h) {                     // the outermost hop is the widest
     const double expect = std::min(1.0, 1.25 * (double)s->fill_ratio[h]) * (double)sl.total_slots[h];
     // (visit-once steps: only on request.  Taking the inserts out of the place phase of the outermost hop - which shares
@@ -1212,7 +1213,17 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     const bool split = s->insert_policy == 1 || (s->insert_policy == 0 && fits && (wide || narrow));
     if (split) { sl.insert_hops |= 1u << h; ++phases; }
   }
-  sl.items.build(L, scan_hops, sl.insert_hops, chain);
+  // A blocking step has its launches to itself: mark and emit share one, the settle phase (128- and 1,024-seed steps
+  // -13 .. -8 %, 65,536-seed steps -8 %).  On graphs with several relations only where a hop is small: the tiles of large
+  // hops outnumber the workgroups there, and looking at each three times costs more than a launch (the seven-relation
+  // workload +9 %).  Next to other steps' phases the waiting workgroups cost more than the launch they save (1,024-seed
+  // steps +7 .. +17 %), but for hops whose emit phase would not scan the tile totals itself (65,536-seed steps -4 %).
+  uint32_t settle_hops = 0;
+  for (int h = 0; h < L && !chain; ++h) {
+    const double tiles = std::min(1.0, 1.1 * (double)s->fill_ratio[h]) * (double)(sl.total_slots[h] / TILE);
+    if (R == 1 ? s->blocking_call || tiles > (double)EMIT_SCAN_TILES : s->blocking_call && tiles <= SETTLE_TYPED_TILES) settle_hops |= 1u << h;
+  }
+  sl.items.build(L, 0u, sl.insert_hops, chain, settle_hops);
 
   // ---- Alg. 3: full refresh when the refresh epoch changes, into the set of tables that is not in use
   //      (stream order puts it after the steps that last read that set: their phases are all issued) ----

@@ -9,9 +9,12 @@
 namespace gss {
 
 constexpr uint32_t EDGE_BIT = 0x80000000u;   // order words: < EDGE_BIT frontier index, >= EDGE_BIT pick slot
-constexpr int TILE = 1024;                    // pick slots per tile (mark and emit phases)
+constexpr int TILE = 1024;                    // pick slots per tile (insert, place and settle phases)
 constexpr int TILE_THREADS = 256;
-constexpr int EMIT_SCAN_MAX_TILES = 4096;       // up to this many tiles per hop, the emit phase scans the tile totals itself
+constexpr int COUNT_STRIDE = 32;        // words between two counters: one 128-byte line each (atomics on one line serialise)
+constexpr int DONE_WAYS = 16;                 // mark phase: counters that find the last workgroup
+constexpr int EMIT_SCAN_TILES = 1024;           // up to this many tiles the emit phase scans the tile totals itself (one relation)
+constexpr int LOOKBACK_BLOCK = 4096;            // settle phase: tiles between two running totals
 
 enum Purpose : uint32_t { P_FILL_FULL = 0, P_FILL_PART = 1, P_EVICT = 2, P_PICK = 3, P_FBL = 4, P_FETCH = 5 };
 
@@ -19,7 +22,7 @@ enum Purpose : uint32_t { P_FILL_FULL = 0, P_FILL_PART = 1, P_EVICT = 2, P_PICK 
 enum : int { ST_ERROR = 0, ST_TICKET = 1, ST_COUNTS = 4 };
 enum : int {
   ERR_SEED_RANGE = 1, ERR_SEED_DUP = 2, ERR_TABLE_FULL = 4, ERR_TABLE_MISS = 8, ERR_GRAPH = 16,
-  ERR_REJECT_OVERFLOW = 32
+  ERR_REJECT_OVERFLOW = 32, ERR_HANDOFF = 64
 };
 
 struct __attribute__((aligned(16))) HashEntry {
@@ -61,7 +64,7 @@ struct TypeParam {
   int32_t frontier_cap;     // allocated length of `frontier` (an upper bound of the frontier size)
 };
 
-// A step is a chain of phases: per hop sample -> mark -> [scan ->] emit.  The kernels of one phase
+// A step is a chain of phases: per hop sample -> [insert ->] mark -> emit (or settle).  The kernels of one phase
 // are latency-bound and leave most of the chip idle, so ONE launch ("tick") carries a phase of every
 // step in flight that is ready for it: one "slice" each, with its own arguments and its own range of workgroups.
 // Stream order between ticks provides every dependency; the host only picks which phases share a tick.
@@ -73,27 +76,31 @@ struct HopCommon {
   int32_t* state;
   int32_t* state_host;      // pinned host copy of `state`, written by the last hop's emit phase (or null)
   int32_t* picks;           // [slots] sampled global id or -1
-  uint32_t* order;          // [slots] order word of the pick's id
-  uint32_t* ranks;          // [slots] rank among firsts (lo 16) / among edges (hi 16) within the tile
-  int32_t* partial_first;   // [tiles]
-  int32_t* partial_edge;
+  // (settle's words carry tags and live in memory that nothing else writes: a foreign word could pass for a tagged one)
   union {
-    struct {                // scan and emit phases
-      int32_t* first_off;
-      int32_t* edge_off;
-    };
-    struct {                // place phase of a visit-once step: the hop's part of the holding area, the step's visit
-      const int32_t* held;  // table (node -> holding index, see ChainArgs)
-      const uint64_t* visit;
-    };
+    uint64_t* agg;          // settle: [tiles] tile totals, with tags
+    uint32_t* tile_sums;    // mark, emit: [tiles] tile totals
   };
+  union {
+    uint64_t* recs;         // settle: [slots / 16] numbers of the first occurrences, with tags
+    uint32_t* ranks;        // mark, emit: the same within a tile
+  };
+  uint32_t* order;          // mark, emit: [slots] order word of the pick's id
+  uint2* tile_off;          // mark, emit: [tiles] new nodes and edges before the tile
+  union {
+    uint64_t* pref;         // settle: running totals after every LOOKBACK_BLOCK tiles, [blocks][R + T]
+    uint32_t* done;         // mark: counters that find the last workgroup, COUNT_STRIDE words apart
+    const int32_t* held;    // place phase of a visit-once step: the hop's part of the holding area, and the step's visit
+  };
+  const uint64_t* visit;    // table (node -> holding index, see ChainArgs)
   int32_t phase;            // Phase
   int32_t gx, gy, gxd, gyd; // the slice's workgroups: gy rows of gx, then gyd rows of gxd
   int32_t R, T;
   int32_t hop, f, k, S;
   int32_t n_new, mode, refresh_now, band_offset;
   int32_t num_tiles_ub, edge_count_off;
-  int32_t scan_in_emit, state_words;
+  uint32_t f_mul;           // 2^20 / f + 1: divides a slot number within a tile by f
+  int32_t state_words;
   int32_t shared, layer;        // shared: one table for all layers, per-layer rank bands; layer: l of this hop
   int32_t insert_split, slot;   // the hop has an insert phase: the sample phase leaves the picks' table inserts to it; slot: the step's slot
   uint32_t ver, step, layer_word, seed_lo, seed_hi;
@@ -112,18 +119,17 @@ struct HopCommon {
 //                  serialise); the pair of nodes a wavefront works on appends to segment (item index / 2) % CHAIN_SEGS,
 //                  so a segment of list h+1 holds at most ceil(V[h] / (2 CHAIN_SEGS)) * 2 * f[h] entries.
 // The counters come in two sets: a step's first chain phase clears the set that the slot's next step will use.
-// Nothing here decides an output order: the place / mark / emit phases do that from the frontier, exactly as for
+// Nothing here decides an output order: the place / settle phases do that from the frontier, exactly as for
 // other steps.  Which of several picks of a node claims it only decides the node's Q and list position, which no
 // output shows.
 constexpr int CHAIN_MAX_HOPS = 4;
 constexpr int CHAIN_SEGS = 32;
-constexpr int CHAIN_COUNT_STRIDE = 32;       // words between two counters: one 128-byte line each (atomics on one line serialise)
 constexpr int CHAIN_TICK_SLICES = 8;        // most slices of a launch of the build that runs visit-once steps
 struct ChainArgs {
   int32_t* held;
   uint64_t* visit;
   uint64_t* list;
-  uint32_t* counts;                   // [CHAIN_MAX_HOPS][CHAIN_SEGS] of this step, CHAIN_COUNT_STRIDE words apart
+  uint32_t* counts;                   // [CHAIN_MAX_HOPS][CHAIN_SEGS] of this step, COUNT_STRIDE words apart
   uint32_t* counts_next;              // the other set
   uint32_t off[CHAIN_MAX_HOPS];       // start of hop h's picks in `held`
   int32_t V[CHAIN_MAX_HOPS];          // size of hop h's holding index space
@@ -186,12 +192,14 @@ struct SlotConst {
   int32_t* state;
   int32_t* state_host;
   int32_t* picks;
-  uint32_t* order;
+  uint64_t* agg;
+  uint64_t* recs;
+  uint64_t* pref;
+  uint32_t* tile_sums;
   uint32_t* ranks;
-  int32_t* partial_first;
-  int32_t* partial_edge;
-  int32_t* first_off;
-  int32_t* edge_off;
+  uint32_t* order;
+  uint2* tile_off;
+  uint32_t* done;
 };
 struct MonoShared {
   RelConst relc;
@@ -210,7 +218,7 @@ struct MonoSlice {
   int32_t count_override, frontier_cap;
   int32_t num_tiles_ub, gx, gxd, band_offset;
   uint32_t ver, step, layer_word;
-  uint8_t slot, phase, hop, layer, f, n_new, refresh_now, scan_in_emit, insert_split, publish, gy, gyd;
+  uint8_t slot, phase, hop, layer, f, n_new, refresh_now, insert_split, publish, gy, gyd;
 };
 template <int D>
 struct TickMono {
@@ -221,7 +229,6 @@ struct TickMono {
 };
 constexpr int TICK_MONO_SLICES = 24;
 constexpr int TICK_MAX_SLICES = 24;           // most slices of a launch in any layout
-constexpr int EMIT_OWN_TILES = 16;            // tiles one emit workgroup owns at most when it scans the tile totals in LDS
 // Largest number of slices one launch can carry for a graph with R relations and T node types.
 int tick_capacity(int R, int T);
 

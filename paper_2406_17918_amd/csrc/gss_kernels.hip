@@ -8,9 +8,9 @@
 //     sample  per frontier node (one half-wavefront): read the cached row, partial refresh (Alg. 2
 //             RefreshCache / OTF-Partial / shared rho-refresh), draw the fanout (SampleFromCache),
 //             write the picks and insert them into the dedupe table;
-//     mark    per pick: look up the table, flag first occurrences, per-tile ranks and tile totals;
-//     scan    (only hops with more than EMIT_SCAN_MAX_TILES tiles) tile totals -> offsets, one workgroup;
-//     emit    per pick: local ids, COO in (dst-major, slot-minor) order, new src_nodes, counts.
+//     mark    per pick: look up the table, flag first occurrences, ranks and totals per tile, offsets, counts;
+//     emit    per pick: local ids, COO in (dst-major, slot-minor) order, new src_nodes;
+//     settle  mark and emit in one launch, for steps that have the launches to themselves.
 //
 // Nothing here is a dense contraction, so no MFMA: the work is row reads, keyed integer hashing
 // (Philox4x32-10), group-level ranking through LDS broadcasts and ballots, and atomics on the dedupe table.
@@ -573,13 +573,20 @@ __device__ __forceinline__ int frontier_count(const HP& P, int t) {
 struct LiveLds {
   int first[GSS_MAX_RELATIONS + 1];
   uint32_t nslots[GSS_MAX_RELATIONS];
+  int base[GSS_MAX_RELATIONS + 1];       // first tile of a relation, dead tiles counted; base[R] = all tiles
+  int src_type[GSS_MAX_RELATIONS];
 };
 template <class HP>
 __device__ __forceinline__ void live_tiles_setup(const HP& P, LiveLds* L) {
+  if constexpr (HP::MAX_R == 1) return;          // one relation: nothing to look up (live_count, live_tile)
   if ((int)threadIdx.x < P.R) {
     // (P is indexed with uniform indices only: a per-lane index would move the arguments to scratch memory)
-    int dst_type = 0;
-    for (int q = 0; q < P.R; ++q) if ((int)threadIdx.x == q) dst_type = rel_of(P, q).dst_type;
+    int dst_type = 0, src_type = 0, base = 0;
+    for (int q = 0; q < P.R; ++q)
+      if ((int)threadIdx.x == q) { dst_type = rel_of(P, q).dst_type; src_type = rel_of(P, q).src_type; base = rel_of(P, q).slot_base / TILE; }
+    L->base[threadIdx.x] = base;
+    L->src_type[threadIdx.x] = src_type;
+    if (threadIdx.x == 0) L->base[P.R] = P.num_tiles_ub;
     int count = -1;
     for (int t = 0; t < P.T; ++t) if (dst_type == t) count = type_of(P, t).count_override;
     if (count < 0) count = P.state[ST_COUNTS + P.hop * P.T + dst_type];
@@ -593,18 +600,25 @@ __device__ __forceinline__ void live_tiles_setup(const HP& P, LiveLds* L) {
   }
   __syncthreads();
 }
-struct LiveTile { int r; uint32_t tile, local0, nslots; };
+// Number of live tiles of the hop.
+template <class HP>
+__device__ __forceinline__ int live_count(const HP& P, const LiveLds* L) {
+  if constexpr (HP::MAX_R == 1) return (int)(((uint32_t)frontier_count(P, 0) * (uint32_t)P.f + TILE - 1) / TILE);
+  return L->first[P.R];
+}
+// Live index of relation r's first tile.
+template <class HP>
+__device__ __forceinline__ int live_first(const LiveLds* L, int r) {
+  if constexpr (HP::MAX_R == 1) return 0;
+  return L->first[r];
+}
+struct LiveTile { int r; uint32_t local0, nslots; };
 template <class HP>
 __device__ __forceinline__ LiveTile live_tile(const HP& P, const LiveLds* L, int j) {
+  if constexpr (HP::MAX_R == 1) return LiveTile{0, (uint32_t)j * TILE, (uint32_t)frontier_count(P, 0) * (uint32_t)P.f};
   int r = 0;
   while (r + 1 < P.R && j >= L->first[r + 1]) ++r;
-  LiveTile t;
-  t.r = r;
-  const uint32_t tl = (uint32_t)(j - L->first[r]);
-  t.tile = (uint32_t)(rel_of(P, r).slot_base / TILE) + tl;
-  t.local0 = tl * TILE;
-  t.nslots = L->nslots[r];
-  return t;
+  return LiveTile{r, (uint32_t)(j - L->first[r]) * TILE, L->nslots[r]};
 }
 
 // ------------------------------------------------------------------------------------------
@@ -938,10 +952,10 @@ __device__ __forceinline__ void chain_phase(const HP& P, const ChainArgs& C, con
   const uint32_t nseeds = first_list == 0 ? F0 : 0u;
   const int h0 = first_list > 1 ? first_list : 1;        // first list kept in segments
   const int nsegs = c >= h0 ? (c - h0 + 1) * CHAIN_SEGS : 0;
-  if (c == 0 && wg.x == 0 && threadIdx.x < CHAIN_MAX_HOPS * CHAIN_SEGS) C.counts_next[threadIdx.x * CHAIN_COUNT_STRIDE] = 0u;
+  if (c == 0 && wg.x == 0 && threadIdx.x < CHAIN_MAX_HOPS * CHAIN_SEGS) C.counts_next[threadIdx.x * COUNT_STRIDE] = 0u;
   if (nsegs > 0) {
     if ((int)threadIdx.x < nsegs) {
-      const uint32_t n = C.counts[(h0 * CHAIN_SEGS + (int)threadIdx.x) * CHAIN_COUNT_STRIDE];
+      const uint32_t n = C.counts[(h0 * CHAIN_SEGS + (int)threadIdx.x) * COUNT_STRIDE];
       const uint32_t cap = C.lcap[h0 + (int)threadIdx.x / CHAIN_SEGS];
       if (n > cap) atomicOr(&P.state[ST_ERROR], ERR_TABLE_FULL);
       CL->start[threadIdx.x + 1] = n < cap ? n : cap;
@@ -1027,7 +1041,7 @@ __device__ __forceinline__ void chain_phase(const HP& P, const ChainArgs& C, con
       const uint32_t seg = (g >> 1) % CHAIN_SEGS;
       const int leader = __ffsll((unsigned long long)wm) - 1;
       uint32_t base = 0u;
-      if (lane_id() == leader) base = atomicAdd(&C.counts[((c + 1) * CHAIN_SEGS + seg) * CHAIN_COUNT_STRIDE], (uint32_t)__popcll(wm));
+      if (lane_id() == leader) base = atomicAdd(&C.counts[((c + 1) * CHAIN_SEGS + seg) * COUNT_STRIDE], (uint32_t)__popcll(wm));
       base = (uint32_t)__shfl((int)base, leader);
       if (won) {
         const uint32_t at = base + (uint32_t)__popcll(wm & ((1ull << lane_id()) - 1ull));
@@ -1051,7 +1065,7 @@ __device__ __forceinline__ void place_phase(const HP& P, const Wg wg, LiveLds* l
   const TypeParam& TP = type_of(P, 0);
   const uint32_t f = (uint32_t)P.f;
   const bool staged = (P.insert_split & 2) != 0;
-  for (int j = wg.x; j < live->first[1]; j += P.gx) {
+  for (int j = wg.x; j < live_count(P, live); j += P.gx) {
     const LiveTile lt = live_tile(P, live, j);
     const uint32_t nslots = lt.nslots;
     const uint32_t g = lt.local0 + ITEMS_PER_THREAD * threadIdx.x;       // one relation: its slots start at 0
@@ -1107,7 +1121,7 @@ __device__ __forceinline__ void insert_phase(const HP& P, const Wg wg, LiveLds* 
     pv_first = *reinterpret_cast<const int4*>(P.picks + (uint32_t)rel_of(P, 0).slot_base + (uint32_t)wg.x * TILE + 4u * threadIdx.x);
   live_tiles_setup(P, live);
   if (!STAGED || (P.insert_split & 2) == 0) {
-    for (int j = wg.x; j < live->first[P.R]; j += P.gx) {
+    for (int j = wg.x; j < live_count(P, live); j += P.gx) {
       const LiveTile lt = live_tile(P, live, j);
       const RelParam& RP = rel_of(P, lt.r);
       const uint32_t nslots = lt.nslots;
@@ -1125,7 +1139,7 @@ __device__ __forceinline__ void insert_phase(const HP& P, const Wg wg, LiveLds* 
   }
   // with the LDS stage: every thread of the workgroup takes part in every tile (barriers)
   if constexpr (STAGED)
-  for (int j = wg.x; j < live->first[P.R]; j += P.gx) {
+  for (int j = wg.x; j < live_count(P, live); j += P.gx) {
     const LiveTile lt = live_tile(P, live, j);
     const RelParam& RP = rel_of(P, lt.r);
     const uint32_t nslots = lt.nslots;
@@ -1148,13 +1162,6 @@ __device__ __forceinline__ void insert_phase(const HP& P, const Wg wg, LiveLds* 
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// mark phase: tiles of TILE pick slots.  For every valid pick: order word of its id in the
-// dedupe table, first-occurrence flag, ranks within the tile.  Tile totals go to `partial_*`.
-// (A "last workgroup done" hand-off inside this kernel was measured and rejected: a device-scope
-// fence per workgroup costs 1-15 us under load, a separate one-workgroup launch costs 2.4 us.)
-// ------------------------------------------------------------------------------------------
-
 // exclusive scan of two small counters over a 256-thread workgroup; returns totals in tot0/tot1
 __device__ __forceinline__ void block_scan2(int v0, int v1, int& ex0, int& ex1, int& tot0, int& tot1, int* lds) {
   const int lane = lane_id(), w = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -1176,219 +1183,567 @@ __device__ __forceinline__ void block_scan2(int v0, int v1, int& ex0, int& ex1, 
   ex0 = b0 + i0 - v0; ex1 = b1 + i1 - v1; tot0 = t0; tot1 = t1;
 }
 
-constexpr int ITEMS = TILE / TILE_THREADS;   // 4 consecutive pick slots per thread: one 16-byte load / store each
-static_assert(ITEMS == 4, "the mark and emit phases move int4 vectors");
+// ------------------------------------------------------------------------------------------
+// mark and emit phases, or settle phase: from the picks of a hop and the dedupe table (complete: an earlier launch did the
+// inserts) to the block, one workgroup per tile of TILE pick slots.  A pick is the first occurrence of its id if the table holds
+// its own slot; the first occurrences are numbered in slot order (after the dst nodes), a repeat takes the number of its first.
+//
+// Lane l of wavefront w owns the slots 256 w + 64 q + l, q = 0 .. 3: a ballot is then a mask of 64 consecutive slots, and
+// ranks are bit counts (no shuffles, no scan).  The numbers of the first occurrences are handed on 16 slots a word (a bit
+// mask and the number of the first one): half a byte per slot or less, where a rank word per slot took four, and small enough
+// for the repeats' random reads to hit the caches.
+//
+// mark, emit (steps that share launches with others): mark stores each pick's order word, the ranks and the tile's totals.
+// Hops of up to EMIT_SCAN_TILES tiles: every workgroup of the emit phase turns the totals into offsets for itself, in LDS (a
+// few KB from L2, next to the loads of its picks).  Larger hops: the workgroup of the mark phase that finishes last does it
+// once.  It is found with counters, and its
+// hand-off needs no fence: the totals are relaxed device-scope atomics, complete before the counter moves.  But the counters
+// are three more round trips at the end of the mark phase: where a launch is short that costs more than the repeated scans
+// (1,024-seed FCR steps on the 169k-node graph: launches of 11.9 us instead of 11.2).
+// settle (blocking steps, which have a launch to themselves): one pass with hand-offs between workgroups, one launch less.  Every
+// hand-off is ONE 64-bit word that carries its own validity (a version tag), stored and loaded with relaxed device-scope
+// atomics: no fence, nothing to clear between hops.
+//   agg[j]    tile j's totals: tag 32 | edges 16 | firsts 16; a tile sums the words of the tiles before it
+//   pref      the running totals after every LOOKBACK_BLOCK tiles (per relation, per node type): a tile reads at most
+//             LOOKBACK_BLOCK words, 16 per thread
+//   recs[g / 16]  tag 17 | number of the first one 31 | mask 16
+// A workgroup only waits for workgroups with smaller numbers of the same slice, which start earlier or at the same time
+// (dispatch is in order on every XCD), so the waits end; they are bounded all the same.
+// ------------------------------------------------------------------------------------------
+constexpr int ITEMS = TILE / TILE_THREADS;   // pick slots per thread
+static_assert(ITEMS == 4 && TILE_THREADS == 256, "four wavefronts of four ballots each");
+constexpr uint32_t NO_PICK = 0xFFFFFFFFu;
+constexpr int SPIN_LIMIT = 1 << 20;          // polls of a hand-off word (about a microsecond each) before giving up
 
-template <class HP>
-__device__ __forceinline__ void mark_phase(const HP& P, const Wg wg, int* lds, LiveLds* live) {
-  // (the first tile's picks are requested ahead of the live counts, as in the insert phase)
-  int4 pv_first = make_int4(-1, -1, -1, -1);
-  if (wg.x < P.num_tiles_ub)
-    pv_first = *reinterpret_cast<const int4*>(P.picks + (uint32_t)rel_of(P, 0).slot_base + (uint32_t)wg.x * TILE + ITEMS * threadIdx.x);
-  live_tiles_setup(P, live);
-  for (int j = wg.x; j < live->first[P.R]; j += P.gx) {
-    const LiveTile lt = live_tile(P, live, j);
-    const RelParam& RP = rel_of(P, lt.r);
-    const uint32_t tile = lt.tile, nslots = lt.nslots;
-    const uint32_t loc = lt.local0 + ITEMS * threadIdx.x;
-    const uint32_t g = (uint32_t)RP.slot_base + loc;
-    const int4 pv = (j == wg.x && lt.r == 0) ? pv_first : *reinterpret_cast<const int4*>(P.picks + g);   // (the buffer covers whole tiles)
-    const uint32_t key_off = type_of(P, RP.src_type).key_off;
-    int id[ITEMS] = {pv.x, pv.y, pv.z, pv.w};
-    uint32_t w[ITEMS];
-    int first[ITEMS], valid[ITEMS];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (loc + j >= nslots) id[j] = -1;
-      valid[j] = id[j] >= 0 ? 1 : 0;
-      w[j] = 0;
-    }
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j)               // four independent table reads in flight
-      if (valid[j]) w[j] = table_lookup(P.ht, P.ver, key_off + (uint32_t)id[j], P.state);
-    int nf = 0, ne = 0;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      first[j] = (valid[j] && w[j] == (EDGE_BIT | (g + j))) ? 1 : 0;
-      nf += first[j]; ne += valid[j];
-    }
-    int exf, exe, tf, te;
-    block_scan2(nf, ne, exf, exe, tf, te, lds);
-    uint32_t rk[ITEMS];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      rk[j] = (uint32_t)exf | ((uint32_t)exe << 16);
-      exf += first[j]; exe += valid[j];
-    }
-    if (loc < nslots) {
-      *reinterpret_cast<uint4*>(P.order + g) = make_uint4(w[0], w[1], w[2], w[3]);
-      *reinterpret_cast<uint4*>(P.ranks + g) = make_uint4(rk[0], rk[1], rk[2], rk[3]);
-    }
-    if (threadIdx.x == 0) { P.partial_first[tile] = tf; P.partial_edge[tile] = te; }
+__device__ __forceinline__ void store_relaxed(uint64_t* p, uint64_t v) {
+  __hip_atomic_store((unsigned long long*)p, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Waits until word *p, last seen as `w`, carries `tag` above bit SHIFT.
+template <int SHIFT>
+__device__ __forceinline__ uint64_t await_word(const uint64_t* p, uint64_t w, uint32_t tag, int32_t* state) {
+  int polls = 0;
+  while ((uint32_t)(w >> SHIFT) != tag) {
+    if (++polls > SPIN_LIMIT) { atomicOr(&state[ST_ERROR], ERR_HANDOFF); return 0ull; }
+    __builtin_amdgcn_s_sleep(1);
+    w = load_relaxed(p);
   }
+  return w;
 }
 
-// Tile totals -> exclusive offsets and the hop's counts.  First occurrences run over the relations
-// of one source node type in ascending order; edges restart per relation.  store(relation, tile within the
-// relation, tile, first_off, edge_off) receives the offsets; when `write_counts`, num_src per node type (= next frontier size)
-// and num_edges per relation go to the device state.
-template <class HP, class Store>
-__device__ __forceinline__ void scan_tiles(const HP& P, const LiveLds* live, Store store, bool write_counts, int* lds) {
-  const int nthreads = (int)blockDim.x;
+struct SettleLds {
+  uint32_t wave[4];                          // firsts | edges << 16 of the tile, per wavefront
+  uint32_t sum_first[4], sum_edge[4];        // sums over the tiles before, per wavefront
+  uint32_t tot_first[GSS_MAX_NODE_TYPES], tot_edge[GSS_MAX_RELATIONS];
+  union {
+    uint64_t recs[TILE / 16];                // settle: the tile's own words of recs[]
+    struct {                                 // mark, emit: scratch of the offsets' scan
+      int scan[32];
+      uint32_t rel_first[GSS_MAX_RELATIONS], add_first[GSS_MAX_RELATIONS], add_edge[GSS_MAX_RELATIONS];
+    };
+    int is_last;
+  };
+  uint2 off[EMIT_SCAN_TILES];                // emit: new nodes and edges before a tile
+};
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o);
+  return v;
+}
+
+// Sums of the firsts / edges words of the tiles [from, to) over the workgroup; of the firsts only those of the relations
+// in the set `same`, of the edges only those of tiles >= edge_from.  (One barrier inside; L->sum_* must be free.)
+template <class HP>
+__device__ __forceinline__ void sum_tiles(const HP& P, const LiveLds* live, SettleLds* L, int from, int to, uint32_t same, int edge_from,
+                                          uint32_t& firsts, uint32_t& edges) {
+  uint32_t sf = 0u, se = 0u;
+  for (int i = from + (int)threadIdx.x; i < to; i += TILE_THREADS) {
+    const uint32_t v = (uint32_t)await_word<32>(P.agg + i, load_relaxed(P.agg + i), P.ver, P.state);
+    bool count_first = true;
+    if constexpr (HP::MAX_R > 1) {
+      int r = 0;
+      while (r + 1 < P.R && i >= live->first[r + 1]) ++r;
+      count_first = (same >> r) & 1u;
+    }
+    if (count_first) sf += v & 0xFFFFu;
+    if (HP::MAX_R == 1 || i >= edge_from) se += v >> 16;
+  }
+  sf = wave_sum(sf);
+  se = wave_sum(se);
+  if (lane_id() == 0) { L->sum_first[threadIdx.x >> 6] = sf; L->sum_edge[threadIdx.x >> 6] = se; }
+  __syncthreads();
+  firsts = L->sum_first[0] + L->sum_first[1] + L->sum_first[2] + L->sum_first[3];
+  edges = L->sum_edge[0] + L->sum_edge[1] + L->sum_edge[2] + L->sum_edge[3];
+}
+
+// Relations with source type s, as a bit set.
+template <class HP>
+__device__ __forceinline__ uint32_t relations_from(const HP& P, int s) {
+  if constexpr (HP::MAX_R == 1) return 1u;
+  uint32_t m = 0u;
+  for (int q = 0; q < P.R; ++q) m |= (rel_of(P, q).src_type == s ? 1u : 0u) << q;
+  return m;
+}
+
+// The hop's counts (num_src per node type = the next frontier, num_edges per relation) from the totals in tot_*, and,
+// after the last hop, the device state (counts of every hop, error flag) to pinned host memory: the step needs no copy
+// command after its kernels.
+template <class HP>
+__device__ __forceinline__ void write_counts(const HP& P, const uint32_t* tot_first, const uint32_t* tot_edge) {
+  if (threadIdx.x == 0) {
+    for (int r = 0; r < P.R; ++r) P.state[ST_COUNTS + P.edge_count_off + P.hop * P.R + r] = (int32_t)tot_edge[r];
+    for (int s = 0; s < P.T; ++s) P.state[ST_COUNTS + (P.hop + 1) * P.T + s] = frontier_count(P, s) + (int32_t)tot_first[s];
+  }
+  if (P.state_host == nullptr) return;
+  __syncthreads();   // this workgroup's own count stores are visible to all its threads
+  for (int i = (int)threadIdx.x; i < P.state_words; i += (int)blockDim.x)
+    P.state_host[i] = i == ST_ERROR ? __hip_atomic_load(&P.state[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : P.state[i];
+}
+template <class HP>
+__device__ __forceinline__ void write_zero_counts(const HP& P, SettleLds* L) {
+  for (int i = (int)threadIdx.x; i < GSS_MAX_RELATIONS; i += TILE_THREADS) L->tot_edge[i] = 0u;
+  for (int i = (int)threadIdx.x; i < GSS_MAX_NODE_TYPES; i += TILE_THREADS) L->tot_first[i] = 0u;
+  __syncthreads();
+  write_counts(P, L->tot_first, L->tot_edge);
+}
+
+// Order word of every pick of the thread in tile `lt` (first slot g0 + own); NO_PICK where a slot holds none (order words are
+// smaller).  The picks themselves are read again where they are needed: registers are what limits this kernel.
+template <class HP>
+__device__ __forceinline__ void load_order_words(const HP& P, const LiveTile& lt, uint32_t g0, uint32_t own, bool have, const int* ahead, uint32_t* w) {
+  const uint32_t key_off = type_of(P, rel_of(P, lt.r).src_type).key_off;
+  int id[ITEMS];
+#pragma unroll
+  for (int q = 0; q < ITEMS; ++q) {
+    const uint32_t s = own + 64u * q;
+    id[q] = -1;
+    if (lt.local0 + s < lt.nslots) id[q] = have ? ahead[q] : P.picks[g0 + s];
+  }
+#pragma unroll
+  for (int q = 0; q < ITEMS; ++q) {               // four independent table reads in flight
+    w[q] = NO_PICK;
+    if (id[q] >= 0) w[q] = table_lookup(P.ht, P.ver, key_off + (uint32_t)id[q], P.state);
+  }
+}
+// First occurrences and picks among the wavefront's slots.
+__device__ __forceinline__ void count_wave(const uint32_t* w, uint32_t mine, uint32_t& nf, uint32_t& ne) {
+  nf = ne = 0u;
+#pragma unroll
+  for (int q = 0; q < ITEMS; ++q) {
+    nf += (uint32_t)__popcll(__ballot(w[q] == mine + 64u * q));
+    ne += (uint32_t)__popcll(__ballot(w[q] != NO_PICK));
+  }
+}
+// Lane l < 16 of a wavefront: mask of the first occurrences among the slots 16 l .. 16 l + 15, and the number of the first
+// of them, `num` being that of the wavefront's first.
+__device__ __forceinline__ uint32_t firsts_of_16(const uint32_t* w, uint32_t mine, int lane, uint32_t& num) {
+  uint64_t m = 0ull, below = 0ull;
+#pragma unroll
+  for (int q = 0; q < ITEMS; ++q) {
+    const uint64_t b = __ballot(w[q] == mine + 64u * q);
+    if (lane >= 4 * q) { num += (uint32_t)__popcll(below); m = b; }
+    below = b;
+  }
+  const int sh = 16 * (lane & 3);
+  num += (uint32_t)__popcll(m & ((1ull << sh) - 1ull));
+  return (uint32_t)(m >> sh) & 0xFFFFu;
+}
+
+// Tile totals -> offsets (off[tile]: new nodes and edges before it) and totals (L->tot_*), by one workgroup.  First
+// occurrences run over the relations of one source type in ascending order; edges restart per relation.  Four tiles per thread
+// and turn.  (FRESH: the totals were written in this launch.)
+template <bool FRESH, class HP>
+__device__ __forceinline__ void scan_tiles(const HP& P, const LiveLds* live, SettleLds* L, uint2* off) {
   for (int s = 0; s < P.T; ++s) {
     int run_first = 0;
     for (int r = 0; r < P.R; ++r) {
-      const RelParam& RP = rel_of(P, r);
-      if (RP.src_type != s) continue;
-      const int ntiles = live->first[r + 1] - live->first[r];
-      const int tbase = RP.slot_base / TILE;
+      if (rel_of(P, r).src_type != s) continue;
+      const int ntiles = HP::MAX_R == 1 ? live_count(P, live) : live->first[r + 1] - live->first[r];
+      const uint32_t* const agg = P.tile_sums + rel_of(P, r).slot_base / TILE;
+      uint2* const to = off + rel_of(P, r).slot_base / TILE;
       int run_edge = 0;
-      for (int c = 0; c < ntiles; c += nthreads) {
-        const int t = c + (int)threadIdx.x;
-        int pf = 0, pe = 0;
-        if (t < ntiles) { pf = P.partial_first[tbase + t]; pe = P.partial_edge[tbase + t]; }
+      for (int c = 0; c < ntiles; c += 4 * TILE_THREADS) {
+        const int t0 = c + 4 * (int)threadIdx.x;
+        int pf[4], pe[4], sf = 0, se = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          uint32_t v = 0u;
+          if (t0 + q < ntiles) v = FRESH ? __hip_atomic_load(agg + t0 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : agg[t0 + q];
+          pf[q] = (int)(v & 0xFFFFu); pe[q] = (int)(v >> 16);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { sf += pf[q]; se += pe[q]; }
         int exf, exe, tf, te;
-        block_scan2(pf, pe, exf, exe, tf, te, lds);
-        if (t < ntiles) store(r, t, tbase + t, run_first + exf, run_edge + exe);
+        block_scan2(sf, se, exf, exe, tf, te, L->scan);
+        exf += run_first; exe += run_edge;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (t0 + q < ntiles) to[t0 + q] = make_uint2((uint32_t)exf, (uint32_t)exe);
+          exf += pf[q]; exe += pe[q];
+        }
         run_first += tf; run_edge += te;
+        if (c + 4 * TILE_THREADS < ntiles) __syncthreads();
       }
-      if (write_counts && threadIdx.x == 0) P.state[ST_COUNTS + P.edge_count_off + P.hop * P.R + r] = run_edge;
+      if (threadIdx.x == 0) L->tot_edge[r] = (uint32_t)run_edge;
+      if constexpr (HP::MAX_R > 1) __syncthreads();
     }
-    if (write_counts && threadIdx.x == 0) P.state[ST_COUNTS + (P.hop + 1) * P.T + s] = frontier_count(P, s) + run_first;
+    if (threadIdx.x == 0) L->tot_first[s] = (uint32_t)run_first;
   }
+  __syncthreads();
 }
 
-// scan phase (one workgroup): only hops with more than EMIT_SCAN_MAX_TILES tiles; otherwise every
-// workgroup of the emit phase scans the tile totals itself, which saves a phase.
+// Do the workgroups of the emit phase scan the tile totals themselves?  (Several relations: only if all tiles, dead ones
+// between the relations included, fit - they are scanned in one go.)
 template <class HP>
-__device__ __forceinline__ void scan_phase(const HP& P, int* lds, LiveLds* live) {
-  live_tiles_setup(P, live);
-  scan_tiles(P, live, [&](int, int, int tile, int fo, int eo) { P.first_off[tile] = fo; P.edge_off[tile] = eo; }, true, lds);
+__device__ __forceinline__ bool scans_in_emit(const HP& P, int ntiles) {
+  return (HP::MAX_R == 1 ? ntiles : P.num_tiles_ub) <= EMIT_SCAN_TILES;
 }
 
-// ------------------------------------------------------------------------------------------
-// emit phase: local ids and COO.  A pick whose id is a dst node has order < EDGE_BIT (the
-// frontier index); otherwise order points at the id's first occurrence g0, whose local id is
-// num_dst + (offset of g0's tile) + (rank of g0 within its tile).
-// ------------------------------------------------------------------------------------------
-// picks / order words / rank words of the four slots a thread owns in a tile
-struct TileRegs { int4 pv; uint4 wv, rv; };
+// scan_tiles for the emit phase of a graph with several relations: ONE scan over the tiles of all relations (a dead tile
+// counts nothing), then the prefix at the start of a relation is taken off again and, for new nodes, the totals of the earlier
+// relations from the same source type are put on.
 template <class HP>
-__device__ __forceinline__ TileRegs load_tile_regs(const HP& P, uint32_t tile) {
-  const uint32_t g = tile * TILE + ITEMS * threadIdx.x;   // relation slot bases are multiples of TILE
-  TileRegs t;
-  t.pv = *reinterpret_cast<const int4*>(P.picks + g);
-  t.wv = *reinterpret_cast<const uint4*>(P.order + g);
-  t.rv = *reinterpret_cast<const uint4*>(P.ranks + g);
-  return t;
-}
-
-// (Loading a tile's vectors before the offsets are known, to overlap them with the tile-total scan,
-// was measured and rejected: launches are sized by upper bounds, and the surplus workgroups' loads
-// cost more than the overlap saves.)
-template <class HP, class IntPtr, class EdgeOff>
-__device__ __forceinline__ void emit_tiles(const HP& P, const Wg wg, const LiveLds* live, IntPtr first_off, EdgeOff edge_off_of) {
-  for (int j = wg.x; j < live->first[P.R]; j += P.gx) {
-    const LiveTile lt = live_tile(P, live, j);
-    const RelParam& RP = rel_of(P, lt.r);
-    const uint32_t tile = lt.tile, nslots = lt.nslots;
-    const uint32_t loc = lt.local0 + ITEMS * threadIdx.x;
-    if (loc >= nslots) continue;
-    const uint32_t g = (uint32_t)RP.slot_base + loc;
-    // three 16-byte loads in flight, then (for picks whose first occurrence is elsewhere) up to four
-    // independent reads of that occurrence's rank word
-    const TileRegs regs = load_tile_regs(P, tile);
-    const int4 pv = regs.pv;
-    const uint4 wv = regs.wv;
-    const uint4 rv = regs.rv;
-    const int num_dst_src = frontier_count(P, RP.src_type);
-    const int eoff = edge_off_of(tile, j);
-    int32_t* __restrict__ src_nodes = type_of(P, RP.src_type).src_nodes;
-    const int id[ITEMS] = {pv.x, pv.y, pv.z, pv.w};
-    const uint32_t w[ITEMS] = {wv.x, wv.y, wv.z, wv.w};
-    const uint32_t rk[ITEMS] = {rv.x, rv.y, rv.z, rv.w};
-    bool valid[ITEMS];
-    uint32_t rk1[ITEMS];
+__device__ __forceinline__ void scan_tiles_of_all(const HP& P, const LiveLds* live, SettleLds* L) {
+  const int t0 = 4 * (int)threadIdx.x;
+  int rel[4], pf[4], pe[4], sf = 0, se = 0;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      valid[j] = loc + j < nslots && id[j] >= 0;
-      rk1[j] = rk[j];
-      if (valid[j] && w[j] >= EDGE_BIT) {
-        const uint32_t g1 = w[j] & ~EDGE_BIT;
-        if (g1 != g + j) rk1[j] = P.ranks[g1];
-      }
-    }
+  for (int q = 0; q < 4; ++q) rel[q] = 0;
+  for (int r = 1; r < P.R; ++r) {
+    const int b = live->base[r];
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (!valid[j]) continue;
-      int lid;
-      if (w[j] < EDGE_BIT) {
-        lid = (int)w[j];                           // a dst node: its frontier index
-      } else {
-        const uint32_t g1 = w[j] & ~EDGE_BIT;
-        lid = num_dst_src + first_off[g1 / TILE] + (int)(rk1[j] & 0xFFFFu);
-        if (g1 == g + j) src_nodes[lid] = id[j];   // the first occurrence publishes the new source node
-      }
-      const int e = eoff + (int)(rk[j] >> 16);
-      RP.src_local[e] = lid;
-      RP.dst_local[e] = (int)((loc + j) / (uint32_t)P.f);
-    }
+    for (int q = 0; q < 4; ++q) rel[q] += t0 + q >= b ? 1 : 0;
   }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = rel[q];
+    uint32_t v = 0u;
+    if (t0 + q - live->base[r] < live->first[r + 1] - live->first[r]) v = P.tile_sums[t0 + q];
+    pf[q] = (int)(v & 0xFFFFu); pe[q] = (int)(v >> 16);
+    sf += pf[q]; se += pe[q];
+  }
+  int exf, exe, tf, te;
+  block_scan2(sf, se, exf, exe, tf, te, L->scan);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    L->off[t0 + q] = make_uint2((uint32_t)exf, (uint32_t)exe);
+    exf += pf[q]; exe += pe[q];
+  }
+  __syncthreads();
+  const int me = (int)threadIdx.x;
+  if (me < 64) {                         // (one wavefront: its LDS operations are in order)
+    volatile uint32_t* const per_rel = L->rel_first;
+    uint2 at = make_uint2(0u, 0u), end = make_uint2((uint32_t)tf, (uint32_t)te);
+    if (me < P.R) {
+      const int b = live->base[me], nb = live->base[me + 1];
+      at = b < EMIT_SCAN_TILES ? L->off[b] : end;
+      if (nb < EMIT_SCAN_TILES && me + 1 < P.R) end = L->off[nb];
+      per_rel[me] = end.x - at.x;
+      L->tot_edge[me] = end.y - at.y;
+      L->add_edge[me] = 0u - at.y;
+    }
+    const int my_type = me < P.R ? live->src_type[me] : -1;
+    uint32_t earlier = 0u, of_type = 0u;
+    for (int q = 0; q < P.R; ++q) {
+      const uint32_t n = per_rel[q];
+      const int s = live->src_type[q];
+      if (q < me && s == my_type) earlier += n;
+      if (s == me) of_type += n;
+    }
+    if (me < P.R) L->add_first[me] = earlier - at.x;
+    if (me < P.T) L->tot_first[me] = of_type;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { L->off[t0 + q].x += L->add_first[rel[q]]; L->off[t0 + q].y += L->add_edge[rel[q]]; }
+  __syncthreads();
 }
 
-// The last hop's workgroup 0 also copies the device state (counts of every hop, error flag) into
-// pinned host memory: the step needs no copy command after its kernels.
+// Is this the last of the n workgroups of the slice that get here?  (Called by all its threads.)  Two levels of counters:
+// additions to one address take 11 ns each.  The last one to see a counter clears it for the next hop.
 template <class HP>
-__device__ __forceinline__ void publish_state(const HP& P, const Wg wg) {
-  if (P.state_host == nullptr || wg.x != 0) return;
-  __syncthreads();   // this workgroup's own count stores are visible to all its threads
-  for (int i = (int)threadIdx.x; i < P.state_words; i += (int)blockDim.x) P.state_host[i] = P.state[i];
+__device__ __forceinline__ bool last_workgroup(const HP& P, const Wg wg, int n, SettleLds* L) {
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the tiles' totals have reached memory
+    const int way = wg.x % DONE_WAYS, ways = min(n, DONE_WAYS), share = n / DONE_WAYS + (way < n % DONE_WAYS ? 1 : 0);
+    uint32_t* c = P.done + (1 + way) * COUNT_STRIDE;
+    bool last = atomicAdd(c, 1u) == (uint32_t)share - 1u;
+    if (last) {
+      *c = 0u;
+      last = atomicAdd(P.done, 1u) == (uint32_t)ways - 1u;
+      if (last) *P.done = 0u;
+    }
+    L->is_last = last ? 1 : 0;
+  }
+  __syncthreads();
+  const bool last = L->is_last != 0;
+  __syncthreads();
+  return last;
 }
 
-// Up to EMIT_SCAN_MAX_TILES tiles, every workgroup turns the tile totals into offsets in its own LDS
-// (a few KB read from L2): first-occurrence offsets of all tiles (any tile may hold the first
-// occurrence of one of this workgroup's picks), edge offsets of its own tiles only.  Workgroup 0 also
-// publishes the hop's counts.
-struct EmitLds {
-  int scan[32];
-  int first_off[EMIT_SCAN_MAX_TILES];
-  int edge_own[EMIT_OWN_TILES];
-};
 template <class HP>
-__device__ __forceinline__ void emit_phase(const HP& P, const Wg wg, EmitLds* L, LiveLds* live) {
+__device__ __forceinline__ void mark_phase(const HP& P, const Wg wg, SettleLds* L, LiveLds* live) {
+  const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+  const uint32_t own = 256u * (uint32_t)wave + (uint32_t)lane;           // first of the thread's slots within a tile
+  // The picks of the workgroup's first tile are requested before the live counts are known: in relation 0 their address
+  // does not depend on them, and the buffer covers every tile of the grid.
+  int ahead[ITEMS];
+  if (wg.x < P.num_tiles_ub) {
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) ahead[q] = P.picks[(uint32_t)wg.x * TILE + own + 64u * q];
+  }
   live_tiles_setup(P, live);
-  // (the grid is sized by an estimate: a workgroup beyond the live tiles has nothing to emit; workgroup 0 stays
-  // for the hop's counts)
-  if (wg.x >= live->first[P.R] && wg.x != 0) return;
-  if (!P.scan_in_emit) {            // offsets were produced by the scan phase
-    const int32_t* eo = P.edge_off;
-    emit_tiles(P, wg, live, (const int32_t*)P.first_off, [=](uint32_t tile, int) { return eo[tile]; });
-    publish_state(P, wg);
+  const int ntiles = live_count(P, live);
+  if (ntiles == 0) {
+    if (wg.x == 0 && !scans_in_emit(P, 0)) write_zero_counts(P, L);
     return;
   }
-  // the workgroup's own tiles are the live tiles me, me + gx, ...: at most EMIT_OWN_TILES of them
-  const int gx = P.gx, me = wg.x;
-  scan_tiles(P, live, [&](int r, int t, int tile, int fo, int eo) {
-    L->first_off[tile] = fo;
-    const int j = live->first[r] + t;
-    if (j % gx == me) L->edge_own[j / gx] = eo;
-  }, wg.x == 0, L->scan);
-  __syncthreads();
-  emit_tiles(P, wg, live, (const int*)L->first_off, [=](uint32_t, int j) { return L->edge_own[j / gx]; });
-  publish_state(P, wg);
+  if (wg.x >= ntiles) return;
+  for (int j = wg.x; j < ntiles; j += P.gx) {
+    const LiveTile lt = live_tile(P, live, j);
+    const uint32_t g0 = (uint32_t)rel_of(P, lt.r).slot_base + lt.local0;  // (relation slot bases are multiples of TILE)
+    uint32_t w[ITEMS];
+    load_order_words(P, lt, g0, own, j == wg.x && lt.r == 0, ahead, w);
+    const uint32_t mine = EDGE_BIT | (g0 + own);
+    uint32_t nf, ne;
+    count_wave(w, mine, nf, ne);
+    if (j != wg.x) __syncthreads();               // (the words of the tile before have been read)
+    if (lane == 0) L->wave[wave] = nf | (ne << 16);
+    __syncthreads();
+    uint32_t before = 0u, total = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { const uint32_t c = L->wave[q]; if (q < wave) before += c; total += c; }
+    if (threadIdx.x == 0) __hip_atomic_store(P.tile_sums + g0 / TILE, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) P.order[g0 + own + 64u * q] = w[q];
+    uint32_t num = before & 0xFFFFu;
+    const uint32_t mask = firsts_of_16(w, mine, lane, num);
+    if (lane < 16) P.ranks[(g0 >> 4) + 16u * (uint32_t)wave + (uint32_t)lane] = mask | (num << 16);
+  }
+  if (scans_in_emit(P, ntiles)) return;
+  if (last_workgroup(P, wg, min(ntiles, P.gx), L)) {
+    scan_tiles<true>(P, live, L, P.tile_off);
+    write_counts(P, L->tot_first, L->tot_edge);
+  }
+}
+
+// Number of the new node whose first occurrence is slot g, without the offset of the dst nodes.
+template <class HP>
+__device__ __forceinline__ uint32_t number_of(uint32_t rank, uint32_t tile_first, uint32_t g) {
+  return tile_first + (rank >> 16) + (uint32_t)__popc(rank & ((1u << (g & 15u)) - 1u));
+}
+
+template <class HP>
+__device__ __forceinline__ void emit_phase(const HP& P, const Wg wg, SettleLds* L, LiveLds* live) {
+  const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+  const uint32_t own = 256u * (uint32_t)wave + (uint32_t)lane;
+  live_tiles_setup(P, live);
+  const int ntiles = live_count(P, live);
+  // (the grid is sized by an estimate: a workgroup beyond the live tiles has nothing to emit; workgroup 0 stays for the
+  // hop's counts)
+  const bool scans = scans_in_emit(P, ntiles);
+  if (wg.x >= ntiles && !(wg.x == 0 && scans)) return;
+  uint32_t w[ITEMS];
+  auto load_words = [&](int j) {
+    const LiveTile lt = live_tile(P, live, j);
+    const uint32_t g0 = (uint32_t)rel_of(P, lt.r).slot_base + lt.local0;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) w[q] = P.order[g0 + own + 64u * q];
+  };
+  if (wg.x < ntiles) load_words(wg.x);            // (they travel while the totals are scanned)
+  if (scans) {
+    if constexpr (HP::MAX_R == 1) scan_tiles<false>(P, live, L, L->off); else scan_tiles_of_all(P, live, L);
+    if (wg.x == 0) write_counts(P, L->tot_first, L->tot_edge);
+  }
+  for (int j = wg.x; j < ntiles; j += P.gx) {
+    const LiveTile lt = live_tile(P, live, j);
+    const RelParam& RP = rel_of(P, lt.r);
+    const uint32_t g0 = (uint32_t)RP.slot_base + lt.local0;
+    if (j != wg.x) load_words(j);
+    uint32_t e = scans ? L->off[g0 / TILE].y : P.tile_off[g0 / TILE].y;
+    uint32_t rank[ITEMS], tile_first[ITEMS];      // of the pick's first occurrence, four in flight; and the id, if it is the first
+    int id[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+      rank[q] = tile_first[q] = 0u;
+      if (w[q] != NO_PICK && w[q] >= EDGE_BIT) {
+        const uint32_t g1 = w[q] & ~EDGE_BIT;
+        rank[q] = P.ranks[g1 >> 4];
+        tile_first[q] = scans ? L->off[g1 / TILE].x : P.tile_off[g1 / TILE].x;
+        if (g1 == g0 + own + 64u * q) id[q] = P.picks[g1];
+      }
+    }
+    uint32_t ne = 0u;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) ne += (uint32_t)__popcll(__ballot(w[q] != NO_PICK));
+    if (j != wg.x) __syncthreads();
+    if (lane == 0) L->wave[wave] = ne;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) if (q < wave) e += L->wave[q];
+    const uint32_t num_dst = (uint32_t)frontier_count(P, RP.src_type);
+    const uint32_t f = (uint32_t)P.f, i0 = lt.local0 / f, rem0 = lt.local0 - i0 * f;
+    int32_t* __restrict__ src_nodes = type_of(P, RP.src_type).src_nodes;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+      const uint64_t valid = __ballot(w[q] != NO_PICK);
+      if (w[q] != NO_PICK) {
+        uint32_t to = w[q];                       // a dst node: its frontier index
+        if (w[q] >= EDGE_BIT) {
+          const uint32_t g1 = w[q] & ~EDGE_BIT;
+          to = num_dst + number_of<HP>(rank[q], tile_first[q], g1);
+          if (g1 == g0 + own + 64u * q) src_nodes[to] = id[q];     // the first occurrence publishes the new source node
+        }
+        const uint32_t at = e + (uint32_t)__popcll(valid & ((1ull << lane) - 1ull));
+        RP.src_local[at] = (int)to;
+        // slot / f through a multiplication: exact for rem0 + slot < 1088 and f <= 64
+        RP.dst_local[at] = (int)(i0 + (((rem0 + own + 64u * q) * P.f_mul) >> 20));
+      }
+      e += (uint32_t)__popcll(valid);
+    }
+  }
+}
+
+// Running totals up to and including tile j (the last of its block or of the hop) -> L->tot_*: own totals in firsts / edges
+// where there is one relation, else summed up per relation and source type.
+template <class HP>
+__device__ __forceinline__ void totals(const HP& P, const LiveLds* live, SettleLds* L, int j, int b0, uint32_t firsts, uint32_t edges) {
+  if constexpr (HP::MAX_R == 1) {
+    if (threadIdx.x == 0) { L->tot_first[0] = firsts; L->tot_edge[0] = edges; }
+  } else {
+    const uint64_t* prev = P.pref + (size_t)(b0 / LOOKBACK_BLOCK - 1) * (size_t)(P.R + P.T);
+    auto before = [&](int at) { return b0 ? (uint32_t)await_word<32>(prev + at, load_relaxed(prev + at), P.ver, P.state) : 0u; };
+    __syncthreads();
+    if ((int)threadIdx.x < P.T) L->tot_first[threadIdx.x] = before(P.R + (int)threadIdx.x);
+    for (int r = 0; r < P.R; ++r) {
+      uint32_t f_, e_;
+      __syncthreads();
+      sum_tiles(P, live, L, max(b0, live->first[r]), min(j + 1, live->first[r + 1]), ~0u, 0, f_, e_);
+      if (threadIdx.x == 0) {
+        L->tot_edge[r] = e_ + before(r);
+        L->tot_first[rel_of(P, r).src_type] += f_;
+      }
+    }
+  }
+}
+
+template <class HP>
+__device__ __forceinline__ void settle_phase(const HP& P, const Wg wg, SettleLds* L, LiveLds* live) {
+  const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+  const uint32_t own = 256u * (uint32_t)wave + (uint32_t)lane;           // first of the thread's slots within a tile
+  // The picks of the workgroup's tile are requested before the live counts are known: in relation 0 their address does
+  // not depend on them, and the buffer covers every tile of the grid.
+  int ahead[ITEMS];
+  if (wg.x < P.num_tiles_ub) {
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) ahead[q] = P.picks[(uint32_t)wg.x * TILE + own + 64u * q];
+  }
+  live_tiles_setup(P, live);
+  const int ntiles = live_count(P, live);
+  if (ntiles == 0) {
+    if (wg.x == 0) write_zero_counts(P, L);
+    return;
+  }
+  // One tile per workgroup, if the grid - sized by an estimate - has enough of them; else consecutive tiles, and what other
+  // workgroups wait for goes out for all of them first: the totals of every tile, then the numbers of every tile, then the
+  // edges (the tiles are then looked at three times; taken one after the other, every tile would wait for the one before).
+  const int per = (ntiles + P.gx - 1) / P.gx;
+  const int j0 = wg.x * per, n = min(per, ntiles - j0);
+  const uint32_t ver = P.ver, tag17 = P.ver & 0x1FFFFu;
+  for (int it = 0; it < (per > 1 ? 3 * n : n); ++it) {
+    const int turn = it < n ? 0 : it < 2 * n ? 1 : 2, j = j0 + it - turn * n;
+    const bool totals_turn = per == 1 || turn == 0, numbers_turn = per == 1 || turn == 1, edges_turn = per == 1 || turn == 2;
+    const LiveTile lt = live_tile(P, live, j);
+    const RelParam& RP = rel_of(P, lt.r);
+    const uint32_t g0 = (uint32_t)RP.slot_base + lt.local0;              // (relation slot bases are multiples of TILE)
+    uint32_t w[ITEMS];
+    load_order_words(P, lt, g0, own, per == 1 && lt.r == 0, ahead, w);
+    const uint32_t mine = EDGE_BIT | (g0 + own);  // the order word that makes the thread's first slot a first occurrence
+    uint32_t nf, ne;
+    count_wave(w, mine, nf, ne);
+    __syncthreads();                              // (the words of the tile before have been read)
+    if (lane == 0) L->wave[wave] = nf | (ne << 16);
+    __syncthreads();
+    uint32_t before = 0u, total = 0u;             // firsts | edges << 16: of the wavefronts before this one, of the tile
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { const uint32_t c = L->wave[q]; if (q < wave) before += c; total += c; }
+    if (totals_turn && threadIdx.x == 0) store_relaxed(P.agg + j, ((uint64_t)ver << 32) | total);
+    if (!numbers_turn && !edges_turn) continue;
+    // ---- the tiles before: offset of the new nodes of this source type, and of the relation's edges ----
+    const int b0 = j / LOOKBACK_BLOCK * LOOKBACK_BLOCK;
+    uint32_t off_first = 0u, off_edge = 0u;
+    if (j > b0) sum_tiles(P, live, L, b0, j, relations_from(P, RP.src_type), live_first<HP>(live, lt.r), off_first, off_edge);
+    if (b0) {
+      const uint64_t* prev = P.pref + (size_t)(b0 / LOOKBACK_BLOCK - 1) * (size_t)(P.R + P.T);
+      off_edge += (uint32_t)await_word<32>(prev + lt.r, load_relaxed(prev + lt.r), ver, P.state);
+      off_first += (uint32_t)await_word<32>(prev + P.R + RP.src_type, load_relaxed(prev + P.R + RP.src_type), ver, P.state);
+    }
+    const bool last = j == ntiles - 1;
+    const bool block_end = j + 1 == b0 + LOOKBACK_BLOCK;
+    uint32_t e = off_edge + (before >> 16);       // of the wavefront's first edge
+    // ---- numbers of the first occurrences, 16 slots a word ----
+    {
+      uint32_t num = (uint32_t)frontier_count(P, RP.src_type) + off_first + (before & 0xFFFFu);
+      const uint32_t mask = firsts_of_16(w, mine, lane, num);
+      const uint64_t rec = ((uint64_t)tag17 << 47) | ((uint64_t)num << 16) | mask;
+      if (lane < 16 && numbers_turn) {
+        store_relaxed(P.recs + (g0 >> 4) + 16u * (uint32_t)wave + (uint32_t)lane, rec);
+      }
+      if (lane < 16) L->recs[16 * wave + lane] = rec;
+    }
+    if (numbers_turn && (block_end || last)) totals(P, live, L, j, b0, off_first + (total & 0xFFFFu), off_edge + (total >> 16));
+    __syncthreads();
+    if (numbers_turn && block_end && !last && (int)threadIdx.x < P.R + P.T) {
+      const int q = (int)threadIdx.x;
+      store_relaxed(P.pref + (size_t)(b0 / LOOKBACK_BLOCK) * (size_t)(P.R + P.T) + q,
+                    ((uint64_t)ver << 32) | (q < P.R ? L->tot_edge[q] : L->tot_first[q - P.R]));
+    }
+    if (numbers_turn && last) write_counts(P, L->tot_first, L->tot_edge);
+    if (!edges_turn) continue;
+    // ---- the repeats' numbers (first occurrences are never later), four words in flight ----
+    uint64_t rec[ITEMS];
+    int id[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+      const uint32_t g1 = w[q] & ~EDGE_BIT;
+      rec[q] = 0ull;
+      if (w[q] != NO_PICK && w[q] >= EDGE_BIT)
+        rec[q] = (g1 ^ g0) < TILE ? L->recs[(g1 & (TILE - 1)) >> 4] : load_relaxed(P.recs + (g1 >> 4));
+      if (w[q] == mine + 64u * q) id[q] = P.picks[g1];
+    }
+    const uint32_t f = (uint32_t)P.f, i0 = lt.local0 / f, rem0 = lt.local0 - i0 * f;
+    int32_t* __restrict__ src_nodes = type_of(P, RP.src_type).src_nodes;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+      const uint64_t valid = __ballot(w[q] != NO_PICK);
+      if (w[q] != NO_PICK) {
+        uint32_t to = w[q];                       // a dst node: its frontier index
+        if (w[q] >= EDGE_BIT) {
+          const uint32_t g1 = w[q] & ~EDGE_BIT;
+          const uint64_t v = await_word<47>(P.recs + (g1 >> 4), rec[q], tag17, P.state);
+          to = (uint32_t)(v >> 16) & 0x7FFFFFFFu;
+          to += (uint32_t)__popc((uint32_t)v & ((1u << (g1 & 15u)) - 1u));
+          if (w[q] == mine + 64u * q) src_nodes[to] = id[q];     // the first occurrence publishes the new source node
+        }
+        const uint32_t at = e + (uint32_t)__popcll(valid & ((1ull << lane) - 1ull));
+        RP.src_local[at] = (int)to;
+        // slot / f through a multiplication: exact for rem0 + slot < 1088 and f <= 64
+        RP.dst_local[at] = (int)(i0 + (((rem0 + own + 64u * q) * P.f_mul) >> 20));
+      }
+      e += (uint32_t)__popcll(valid);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------
 // step_tick_kernel: a one-dimensional grid holds the workgroups of all slices back to back (slice i
 // owns [end[i-1], end[i]), x-major within its gx * gy rectangle), so no workgroup is launched in vain.
 // ------------------------------------------------------------------------------------------
-template <int W>
+template <int W, bool STAGED>
 union TickLds {
   GroupLdsT<W> group[GrpT<W>::PER_WG];
-  int scan[32];
-  EmitLds emit;
+  SettleLds settle;
+  typename std::conditional<STAGED, DedupeLds, int>::type stage;    // only in the builds with the LDS stage of the dedupe
 };
-static_assert(sizeof(DedupeLds) <= sizeof(EmitLds), "the LDS stage of the dedupe borrows the emit phase's scratch");
 // Scalar registers, not vector registers or LDS, decide how many workgroups a CU holds: with the 106 the
 // compiler takes by itself 6 were resident per CU (measured: 191 per XCD at the peak of a full tick), capped at
 // 96 it is 7 (223 per XCD); the spills go to lanes of a vector register.  Capping further for 8 costs more in
@@ -1404,19 +1759,20 @@ __device__ __forceinline__ void run_slice(const HP& P, int block, const ChainArg
   while (wg.y < P.gy && wg.x >= P.gx) { wg.x -= P.gx; ++wg.y; }
   if (wg.y == P.gy && P.gxd > 0)
     while (wg.x >= P.gxd) { wg.x -= P.gxd; ++wg.y; }
-  __shared__ TickLds<W> lds;
+  constexpr bool STAGED = std::is_base_of<HopParamsStaged, HP>::value;
+  __shared__ TickLds<W, STAGED> lds;
   __shared__ LiveLds live;
   __shared__ typename std::conditional<std::is_same<HP, HopParamsChain>::value && W == 32, ChainLds, int>::type chain_lds;
   (void)chain_lds;
   switch (P.phase) {
     case PH_SAMPLE: sample_phase(P, wg, lds.group); break;
-    case PH_MARK:   mark_phase(P, wg, lds.scan, &live); break;
-    case PH_SCAN:   scan_phase(P, lds.scan, &live); break;
-    case PH_INSERT: insert_phase<std::is_base_of<HopParamsStaged, HP>::value>(P, wg, &live, reinterpret_cast<DedupeLds*>(&lds.emit)); break;
-    case PH_EMIT:   emit_phase(P, wg, &lds.emit, &live); break;
+    case PH_INSERT: insert_phase<STAGED>(P, wg, &live, reinterpret_cast<DedupeLds*>(&lds.stage)); break;
+    case PH_MARK:   mark_phase(P, wg, &lds.settle, &live); break;
+    case PH_EMIT:   emit_phase(P, wg, &lds.settle, &live); break;
+    case PH_SETTLE: settle_phase(P, wg, &lds.settle, &live); break;
     default:
       if constexpr (std::is_same<HP, HopParamsChain>::value && W == 32) {     // (only this build holds the visit-once code)
-        if (P.phase == PH_PLACE) place_phase(P, wg, &live, reinterpret_cast<DedupeLds*>(&lds.emit));
+        if (P.phase == PH_PLACE) place_phase(P, wg, &live, reinterpret_cast<DedupeLds*>(&lds.stage));
         else if (P.phase == PH_CHAIN) chain_phase<!DENSE>(P, *C, wg, lds.group, &chain_lds);
       }
       break;
@@ -1461,16 +1817,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(96))) void step
   H.ht = sc.ht;
   H.state = sc.state;
   H.state_host = c.publish ? sc.state_host : nullptr;
-  H.picks = sc.picks; H.order = sc.order; H.ranks = sc.ranks;
-  H.partial_first = sc.partial_first; H.partial_edge = sc.partial_edge;
-  H.first_off = sc.first_off; H.edge_off = sc.edge_off;
+  H.picks = sc.picks; H.order = sc.order; H.tile_off = sc.tile_off;
+  if (c.phase == PH_SETTLE) { H.agg = sc.agg; H.recs = sc.recs; H.pref = sc.pref; }
+  else { H.tile_sums = sc.tile_sums; H.ranks = sc.ranks; H.done = sc.done; }
   H.phase = c.phase;
   H.gx = c.gx; H.gy = c.gy; H.gxd = c.gxd; H.gyd = c.gyd;
   H.R = 1; H.T = 1;
   H.hop = c.hop; H.f = c.f; H.k = M.h.k; H.S = M.h.S;
   H.n_new = c.n_new; H.mode = M.h.mode; H.refresh_now = c.refresh_now; H.band_offset = c.band_offset;
   H.num_tiles_ub = c.num_tiles_ub; H.edge_count_off = M.h.edge_count_off;
-  H.scan_in_emit = c.scan_in_emit; H.state_words = M.h.state_words;
+  H.f_mul = (1u << 20) / (uint32_t)c.f + 1u; H.state_words = M.h.state_words;
   H.shared = M.h.shared; H.layer = c.layer;
   H.insert_split = c.insert_split; H.slot = c.slot;
   H.ver = c.ver; H.step = c.step; H.layer_word = c.layer_word; H.seed_lo = M.h.seed_lo; H.seed_hi = M.h.seed_hi;
@@ -1790,7 +2146,7 @@ static hipError_t launch_tick_mono(const HopParams* P, int n, const RelConst* re
     c.ver = src.ver; c.step = src.step; c.layer_word = src.layer_word;
     c.slot = (uint8_t)src.slot; c.phase = (uint8_t)src.phase; c.hop = (uint8_t)src.hop; c.layer = (uint8_t)src.layer;
     c.f = (uint8_t)src.f; c.n_new = (uint8_t)src.n_new; c.refresh_now = (uint8_t)src.refresh_now;
-    c.scan_in_emit = (uint8_t)src.scan_in_emit; c.insert_split = (uint8_t)src.insert_split;
+    c.insert_split = (uint8_t)src.insert_split;
     c.publish = src.state_host ? 1 : 0; c.gy = (uint8_t)src.gy; c.gyd = (uint8_t)src.gyd;
     if (src.rel[0].slot_base != 0 || src.f > 255 || src.n_new > 255 || src.gy > 255 || src.gyd > 255)
       return hipErrorInvalidValue;

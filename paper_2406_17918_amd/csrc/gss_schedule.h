@@ -5,13 +5,14 @@
 
 namespace gss {
 
-// A step is a chain of phases: per hop sample -> [insert ->] mark -> [scan ->] emit.
+// A step is a chain of phases: per hop sample -> [insert ->] mark -> [scan ->] emit, or sample -> [insert ->] settle.
 // A "visit-once" step (one table for all hops, refreshed per visit) splits the work differently: its CHAIN phases, one
 // per hop, do everything that touches the cache table - they find the nodes a hop visits for the first time in this
 // step and draw the picks of all their remaining hops at once, into a holding area -, and a list of per-hop phases
 // place -> mark -> [scan ->] emit puts the picks into frontier order, dedupes and emits.  Only the chain phases of
 // consecutive steps depend on each other; the list trails behind and shares launches with the chains of later steps.
-enum Phase : int32_t { PH_SAMPLE = 0, PH_MARK = 1, PH_SCAN = 2, PH_EMIT = 3, PH_INSERT = 4, PH_PLACE = 5, PH_CHAIN = 6 };
+enum Phase : int32_t { PH_SAMPLE = 0, PH_MARK = 1, PH_SCAN = 2, PH_EMIT = 3, PH_INSERT = 4, PH_PLACE = 5, PH_CHAIN = 6,
+                       PH_SETTLE = 7 };
 
 constexpr int SCHED_MAX_LAYERS = 8;
 constexpr int SCHED_MAX_ITEMS = SCHED_MAX_LAYERS * 5;      // per hop at most: sample | place, insert, mark, scan, emit
@@ -27,14 +28,15 @@ struct StepItems {
   // hop h gets a separate scan phase iff bit h of `scan_hops` is set (hops with very many tiles), and a
   // separate insert phase iff bit h of `insert_hops` is set (large hops: the dedupe table inserts leave
   // the sample phase - or the place phase of a visit-once step -, which shortens the longest phase of a launch).
-  // `chain`: a visit-once step.
-  void build(int layers, uint32_t scan_hops, uint32_t insert_hops, bool chain = false) {
+  // `chain`: a visit-once step.  Hops of `settle_hops` end with a settle phase instead of mark, scan and emit.
+  void build(int layers, uint32_t scan_hops, uint32_t insert_hops, bool chain = false, uint32_t settle_hops = 0) {
     L = layers; num_items = 0; next_item = 0;
     num_chain = chain ? layers : 0; next_chain = 0;
     auto push = [&](int h, Phase ph) { item_hop[num_items] = (int8_t)h; item_phase[num_items++] = (int8_t)ph; };
     for (int h = 0; h < layers; ++h) {
       push(h, chain ? PH_PLACE : PH_SAMPLE);
       if ((insert_hops >> h) & 1u) push(h, PH_INSERT);
+      if ((settle_hops >> h) & 1u) { push(h, PH_SETTLE); continue; }
       push(h, PH_MARK);
       if ((scan_hops >> h) & 1u) push(h, PH_SCAN);
       push(h, PH_EMIT);
