@@ -2174,7 +2174,6 @@ hipError_t launch_tick(const HopParams* P, int n, const RelConst* relc_host, con
   const int R = P[0].R, T = P[0].T;
   if (chain_build) {
     if (R != 1 || T != 1 || n > CHAIN_TICK_SLICES) return hipErrorInvalidValue;
-    if (n == 1) return launch_tick_t<HopParamsChain, 1>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     if (n <= 4) return launch_tick_t<HopParamsChain, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     return launch_tick_t<HopParamsChain, CHAIN_TICK_SLICES>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
   }
@@ -2190,25 +2189,20 @@ hipError_t launch_tick(const HopParams* P, int n, const RelConst* relc_host, con
     return launch_tick_mono(P, n, relc_host, slots_dev, st, timer, done);
   }
   if (R == 1 && T == 1) {
-    // (the one-slice builds with narrow groups would spill vector registers when held to 64 of them)
-    if (n == 1) return launch_tick_t<HopParamsMono, 1>(P, n, relc_host, relc_dev, chain, st, timer, done, dense && !narrow, width);
     if (n <= 4) return launch_tick_t<HopParamsMono, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
     if (n <= 8) return launch_tick_t<HopParamsMono, 8>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
     return launch_tick_t<HopParamsMono, 12>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
   }
   if (R <= HopParamsSmall::MAX_R && T <= HopParamsSmall::MAX_T) {
-    if (n == 1) return launch_tick_t<HopParamsSmall, 1>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     if (n <= 3) return launch_tick_t<HopParamsSmall, 3>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     if (n <= 6) return launch_tick_t<HopParamsSmall, 6>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     return launch_tick_t<HopParamsSmall, 9>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
   }
   if (R <= HopParamsMid::MAX_R && T <= HopParamsMid::MAX_T) {
-    if (n == 1) return launch_tick_t<HopParamsMid, 1>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     if (n <= 3) return launch_tick_t<HopParamsMid, 3>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
     return launch_tick_t<HopParamsMid, 6>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
   }
-  if (n == 1) return launch_tick_t<HopParams, 1>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-  if (n == 2) return launch_tick_t<HopParams, 2>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
+  if (n <= 2) return launch_tick_t<HopParams, 2>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
   return launch_tick_t<HopParams, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
 }
 
