@@ -1196,7 +1196,8 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
   //     launch, and the load + atomic of the insert are two more links (the 128-seed workload: -10 % per step);
   //     not with one table for all hops and a refresh, where a step's phases run one after the other and a phase
   //     more is a launch more;
-  //   as long as a tick still fits one launch.
+  //   as long as a tick still fits one launch; and not in blocking steps, where a phase more is a launch more (128-seed
+  //   steps +22 %, 1,024-seed FCR steps +15 %).
   sl.insert_hops = 0;
   int phases = 3 * L;
   for (int h = L - 1; h >= 0; --h) {                     // the outermost hop is the widest
@@ -1205,8 +1206,8 @@ gss_status gss_step_async(gss_sampler* s, const int32_t* seeds, int32_t num_seed
     // a launch with the chain phase of hop 0 and is the longest slice of that launch - was measured on the 4,096-seed
     // shared-table workload: 0.1197 instead of 0.1177 ms per step.  The launches of a full pipeline are bound by the
     // work they hold, not by their longest slice.)
-    const bool wide = !chain && !s->otf && expect >= (double)INSERT_SPLIT_SLOTS;
-    const bool narrow = !chain && !(s->otf && s->shared) && expect <= (double)INSERT_SMALL_SLOTS;
+    const bool wide = !chain && !s->blocking_call && !s->otf && expect >= (double)INSERT_SPLIT_SLOTS;
+    const bool narrow = !chain && !s->blocking_call && !(s->otf && s->shared) && expect <= (double)INSERT_SMALL_SLOTS;
     // (a tick of visit-once steps holds a chain phase and one list phase of each step in flight, whatever the number
     // of a step's phases)
     const bool fits = chain || phases < s->tick_cap;
