@@ -32,9 +32,10 @@ def build_binding(verbose: bool = False) -> str:
     import torch
     base = os.path.dirname(os.path.abspath(torch.__file__))
     inc, lib = os.path.join(base, "include"), os.path.join(base, "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-isystem", inc,
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(rocm, "include"), "-I", os.path.join(ROOT, "include"), "-isystem", inc,
            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
-           os.path.join(CSRC, "gss_torch.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+           os.path.join(CSRC, "gss_torch.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)

@@ -1992,25 +1992,58 @@ __global__ void list_from_map_kernel(const int32_t* __restrict__ map, int64_t n,
 }
 
 // ------------------------------------------------------------------------------------------
-// Feature gather (the value side of the K-V cache: out[i] = H[ids[i]]).  LANES lanes (a power of two)
-// share a row and walk over its 16 / 8 / 4 / 1-byte chunks, so a wavefront reads whole rows with
-// consecutive vector loads; this is the one HBM-bound kernel of the library.
+// Feature gather (the value side of the K-V cache: out[i] = H[ids[i]]), the one HBM-bound kernel of the library.
+// A row is ceil(row_bytes / sizeof(VEC)) chunks, the last one moved back so that it ends with the row (it may repeat bytes
+// of the one before), so every row from sizeof(VEC) bytes on moves in VEC accesses, whatever its length and address: the
+// hardware takes unaligned 16-byte accesses.  (Chosen by alignment instead, rows of an odd number of bf16 values moved byte by
+// byte.)  The chunks of all rows are dealt out to the threads in order: no lane idles however many chunks a row has, and
+// every thread has GATHER_UNROLL rows in flight (1, 2, 4, 8: two and four are within 1 %, eight 5 % slower).  The output is
+// written around the caches (non-temporal stores: nothing of it is read here again, and the table's popular rows keep
+// their place): 133k rows of 400 bytes 21.1 us instead of 24.7 with ordinary stores and 26.3 with 32 lanes per row - 5.05 TB/s,
+// a plain copy reaches 4.8 on this card; 1,501 rows of 5,732 bytes 3.9 us instead of 9.6, 100k rows of 301 bf16 22.6 instead of 77.6.
 // ------------------------------------------------------------------------------------------
+constexpr int GATHER_UNROLL = 2, GATHER_CHUNKS = 256 * GATHER_UNROLL;      // chunks of a workgroup
+template <class VEC> struct __attribute__((packed, aligned(1))) Unaligned { VEC v; };
 template <class VEC>
-__global__ __launch_bounds__(256) void gather_rows_kernel(const VEC* __restrict__ table, int64_t num_rows, int chunks,
-                                                          const int32_t* __restrict__ ids, int64_t num_ids,
-                                                          VEC* __restrict__ out, int lanes_log2) {
-  const int lanes = 1 << lanes_log2;
-  const int rows_per_block = 256 >> lanes_log2;
-  const int c0 = (int)threadIdx.x & (lanes - 1);
-  for (int64_t i = (int64_t)blockIdx.x * rows_per_block + ((int)threadIdx.x >> lanes_log2); i < num_ids;
-       i += (int64_t)gridDim.x * rows_per_block) {
-    const int64_t v = ids[i];
-    const bool ok = v >= 0 && v < num_rows;
-    const VEC* __restrict__ src = table + v * chunks;
-    VEC* __restrict__ dst = out + i * chunks;
-    for (int c = c0; c < chunks; c += lanes) dst[c] = ok ? src[c] : VEC{};
+__device__ __forceinline__ void store_streaming(char* at, const VEC& v) {
+  if constexpr (sizeof(VEC) == 16) {
+    typedef uint32_t Quad __attribute__((ext_vector_type(4), aligned(1)));
+    __builtin_nontemporal_store(Quad{v.x, v.y, v.z, v.w}, reinterpret_cast<Quad*>(at));
+  } else {
+    reinterpret_cast<Unaligned<VEC>*>(at)->v = v;
   }
+}
+template <class VEC>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const char* __restrict__ table, int64_t num_rows, int64_t row_bytes, int chunks,
+                                                          uint32_t inv_chunks, const int32_t* __restrict__ ids, int64_t num_ids,
+                                                          char* __restrict__ out) {
+  // chunk c0 + n of the workgroup, c0 = row0 * chunks + rest: row row0 + (rest + n) / chunks
+  const int64_t c0 = (int64_t)blockIdx.x * GATHER_CHUNKS, row0 = c0 / chunks;
+  const uint32_t rest = (uint32_t)(c0 - row0 * chunks), left = (uint32_t)min(num_ids - row0, (int64_t)0x7FFFFFFF);
+  ids += row0;
+  out += row0 * row_bytes;
+  uint32_t q[GATHER_UNROLL];             // row of the chunk, from row0 on
+  int32_t id[GATHER_UNROLL];
+  VEC v[GATHER_UNROLL];
+  auto within = [&](int u) {             // first byte of the chunk within its row
+    const uint32_t n = rest + 256u * u + threadIdx.x;
+    return min((int64_t)((n - q[u] * (uint32_t)chunks) * (uint32_t)sizeof(VEC)), row_bytes - (int64_t)sizeof(VEC));
+  };
+#pragma unroll
+  for (int u = 0; u < GATHER_UNROLL; ++u) {
+    const uint32_t n = rest + 256u * u + threadIdx.x;
+    q[u] = chunks == 1 ? n : __umulhi(n, inv_chunks);        // n / chunks: exact for n <= 1024 + chunks, chunks <= 2^16
+    id[u] = ids[min(q[u], left - 1u)];
+  }
+#pragma unroll
+  for (int u = 0; u < GATHER_UNROLL; ++u) {
+    const bool ok = (uint32_t)id[u] < (uint32_t)min(num_rows, (int64_t)0x80000000ll);
+    v[u] = reinterpret_cast<const Unaligned<VEC>*>(table + (ok ? (int64_t)id[u] : 0ll) * row_bytes + within(u))->v;
+    if (!ok) v[u] = VEC{};
+  }
+#pragma unroll
+  for (int u = 0; u < GATHER_UNROLL; ++u)
+    if (q[u] < left) store_streaming(out + (int64_t)q[u] * row_bytes + within(u), v[u]);
 }
 
 __global__ void store_slot_kernel(SlotConst* at, SlotConst value) {
@@ -2264,24 +2297,26 @@ hipError_t launch_build_row_map(const void* indptr, int is64, int64_t n, int32_t
 }
 
 template <class VEC>
-static hipError_t launch_gather_t(const void* table, int64_t num_rows, int64_t row_bytes, const int32_t* ids,
-                                  int64_t num_ids, void* out, hipStream_t st) {
-  const int chunks = (int)(row_bytes / (int64_t)sizeof(VEC));
-  int lanes_log2 = 0;
-  while ((1 << lanes_log2) < chunks && lanes_log2 < 6) ++lanes_log2;
-  const int rows_per_block = 256 >> lanes_log2;
-  const unsigned grid = clamp_grid((num_ids + rows_per_block - 1) / rows_per_block, 1 << 20);
-  hipLaunchKernelGGL(gather_rows_kernel<VEC>, dim3(grid), dim3(256), 0, st, (const VEC*)table, num_rows, chunks, ids,
-                     num_ids, (VEC*)out, lanes_log2);
+static hipError_t launch_gather_t(const void* table, int64_t num_rows, int64_t row_bytes, const int32_t* ids, int64_t num_ids,
+                                  void* out, hipStream_t st) {
+  const int chunks = (int)((row_bytes + (int64_t)sizeof(VEC) - 1) / (int64_t)sizeof(VEC));
+  const uint32_t inv = (uint32_t)(((1ull << 32) + (uint64_t)chunks - 1) / (uint64_t)chunks);   // (chunks == 1: not used)
+  const int64_t most = (int64_t)1 << 30;                 // workgroups of a launch
+  const int64_t rows = most * GATHER_CHUNKS / chunks;    // ... and the rows they take
+  for (int64_t i = 0; i < num_ids; i += rows) {
+    const int64_t n = num_ids - i < rows ? num_ids - i : rows, wgs = (n * chunks + GATHER_CHUNKS - 1) / GATHER_CHUNKS;
+    hipLaunchKernelGGL(gather_rows_kernel<VEC>, dim3((unsigned)wgs), dim3(256), 0, st, (const char*)table, num_rows, row_bytes, chunks,
+                       inv, ids + i, n, (char*)out + i * row_bytes);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_gather_rows(const void* table, int64_t num_rows, int64_t row_bytes, const int32_t* ids, int64_t num_ids,
                               void* out, hipStream_t st) {
-  const uintptr_t align = (uintptr_t)table | (uintptr_t)out | (uintptr_t)row_bytes;   // widest vector all three allow
-  if (align % 16 == 0) return launch_gather_t<uint4>(table, num_rows, row_bytes, ids, num_ids, out, st);
-  if (align % 8 == 0) return launch_gather_t<uint2>(table, num_rows, row_bytes, ids, num_ids, out, st);
-  if (align % 4 == 0) return launch_gather_t<uint32_t>(table, num_rows, row_bytes, ids, num_ids, out, st);
+  if (num_rows == 0) table = out;        // (every row is zeros: the kernel reads a row that exists and drops it)
+  if (row_bytes >= 16) return launch_gather_t<uint4>(table, num_rows, row_bytes, ids, num_ids, out, st);
+  if (row_bytes >= 8) return launch_gather_t<uint2>(table, num_rows, row_bytes, ids, num_ids, out, st);
+  if (row_bytes >= 4) return launch_gather_t<uint32_t>(table, num_rows, row_bytes, ids, num_ids, out, st);
   return launch_gather_t<uint8_t>(table, num_rows, row_bytes, ids, num_ids, out, st);
 }
 

@@ -9,6 +9,7 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "gss.h"
@@ -166,14 +167,13 @@ PyObject* py_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return st == GSS_OK ? make_blocks(b, a[5], a[6], a[7]) : PyLong_FromLong(st);
 }
 
-// gather_rows(table, ids, out, stream) -> status; the tensors' devices, types and sizes are checked here
+// gather_rows(table, ids, out) -> status, on the current stream of the table's device; the tensors' devices, types and sizes
+// are checked here
 PyObject* py_gather_rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (!nargs_are(n, 4)) return nullptr;
+  if (!nargs_are(n, 3)) return nullptr;
   for (int i = 0; i < 3; ++i)
     if (!THPVariable_Check(a[i])) { PyErr_SetString(PyExc_TypeError, "gather_rows: torch tensors are expected"); return nullptr; }
   const at::Tensor &table = THPVariable_Unpack(a[0]), &ids = THPVariable_Unpack(a[1]), &out = THPVariable_Unpack(a[2]);
-  void* stream = PyLong_AsVoidPtr(a[3]);
-  if (PyErr_Occurred()) return nullptr;
   const int64_t count = ids.numel(), values = table.numel();
   if (!(table.is_cuda() && ids.is_cuda() && ids.scalar_type() == at::kInt && table.is_contiguous() && ids.is_contiguous() &&
         table.dim() >= 1 && out.is_contiguous() && out.scalar_type() == table.scalar_type() &&
@@ -183,6 +183,7 @@ PyObject* py_gather_rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   int64_t row_bytes = (int64_t)table.itemsize();
   for (int64_t d = 1; d < table.dim(); ++d) row_bytes *= table.size(d);
+  void* const stream = c10::hip::getCurrentHIPStream(table.device().index()).stream();
   gss_status st;
   Py_BEGIN_ALLOW_THREADS
   st = lib.gather_rows(values ? table.data_ptr() : nullptr, table.size(0), row_bytes,

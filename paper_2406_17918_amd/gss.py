@@ -209,11 +209,10 @@ def upload_graph(graph, device="cuda:0") -> List[DeviceRelation]:
 def gather_rows(table, ids, out=None):
     """gss_gather_rows on torch tensors: out[i] = table[ids[i]] (table: [N, ...] contiguous, ids: int32, both on the GPU);
     enqueued on torch's current stream."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty((ids.numel(),) + tuple(table.shape[1:]), dtype=table.dtype, device=table.device)
-    native = _native or load_binding()
-    st = native.gather_rows(table, ids, out, torch._C._cuda_getCurrentRawStream(table.device.index) if table.is_cuda else 0)
+    st = (_native or load_binding()).gather_rows(table, ids, out)
     if st != GSS_OK:
         raise GssError(st, "gss_gather_rows failed")
     return out
