@@ -40,6 +40,7 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 
 __device__ __forceinline__ Block4 philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1,
                                                 uint32_t c2, uint32_t c3) {
+  asm("" : "+s"(k0), "+s"(k1));
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0;   // one 32x32->64 multiply gives hi and lo
@@ -116,7 +117,15 @@ struct GrpT {
   int sub;                 // lane within the group
   int half;                // group within the wavefront
   bool idle;               // a lane beyond the wavefront's last group (only when W does not divide 64): it takes no part
+  int ahead;               // see set_redraws: attempt << 8 | number of the pending slot that the lane draws for
+  int redraws;
   LdsPtr L;
+  // The visits of a phase redraw n slots each (a constant of the launch).  Lane (attempt a, pending slot q) = a * n + q.
+  __device__ __forceinline__ void set_redraws(int n) {
+    redraws = n > 0 ? n : 1;
+    const int a = sub / redraws;
+    ahead = (a << 8) | (sub - a * redraws);
+  }
   __device__ __forceinline__ void init(GroupLdsT<W>* lds) {        // `lds`: one scratch per group of the workgroup
     if constexpr (W == 32 || W == 64) {
       sub = (int)(threadIdx.x & (unsigned)(W - 1));
@@ -190,21 +199,56 @@ __device__ __forceinline__ void grp_rank2(const GrpT<W>& G, int n, uint64_t p0, 
 // adj[pos]; it is accepted unless the id is already in the row or proposed by a lower pending slot
 // in the same round (which is what slot-ascending sequential processing of a round yields).
 // FEW: few slots are pending (a partial refresh): instead of every lane scanning all k slots, the
-// group walks over the pending slots, and every lane compares its own id with that slot's proposal.
-// From eight pending slots down, several rounds are drawn at once (below).
+// group walks over the pending slots, and every lane compares its own id with that slot's proposal.  The n_new pending
+// slots of a visit leave lanes over, which draw the slots' next attempts in the same block (set_redraws): a second round
+// is then a walk over LDS instead of another Philox block and another trip to the adjacency (with n_new = 4 and 32 lanes
+// half of the wavefronts needed one or more).  Up to four attempts where a repeat is likely and the adjacency is a few
+// cache lines (deg < 8 k), two up to deg < 32 k; the neighbors of a hub lie in a line each, and there one attempt nearly
+// always does.
+// From eight pending slots down, the fill of a whole row draws several rounds at once (below).
 template <bool FEW, int W>
 __device__ __forceinline__ int grp_rejection_fill(const GrpT<W>& G, MaskT<W> pend, MaskT<W> fixed, int val, int k,
                                                   const int32_t* __restrict__ adj, uint32_t deg,
                                                   const DrawKey& K, uint32_t purpose, int32_t* state) {
   using Mask = MaskT<W>;
   constexpr int GRP = W;
+  if constexpr (FEW) {
+    const int most = deg < 8u * (uint32_t)k ? 4 : (deg < 32u * (uint32_t)k ? 2 : 1);
+    const int drawn = min(most, GRP / G.redraws);                         // attempts at once: every pending slot has a lane for each
+    for (uint32_t a = 0; pend != 0; a += (uint32_t)drawn) {
+      if (a >= 65536u - 4u) {   // acceptance probability is > 1/2 per draw: unreachable for a simple graph
+        if (G.sub == 0) atomicOr(&state[ST_ERROR], ERR_REJECT_OVERFLOW);
+        break;
+      }
+      if (G.in(pend)) G.L->out[mask_popc(pend & G.below())] = G.sub;
+      const int n = mask_popc(pend), my_a = G.ahead >> 8, my_q = G.ahead & 0xFF;
+      const int slot = G.L->out[my_q];
+      int cand = -3;
+      if (my_a < drawn && my_q < n) cand = adj[below(lo64(draw_block(K, purpose, (uint32_t)slot, a + (uint32_t)my_a)), deg)];
+      G.L->ab[G.sub] = (uint64_t)(uint32_t)cand | ((uint64_t)(uint32_t)slot << 32);
+      Mask open = GrpT<W>::first(n);                                      // pending, by number
+      for (int i = 0; i < drawn && open != 0; ++i)
+        for (Mask m = open; m != 0; m &= m - (Mask)1) {                   // (the same in all lanes of the group)
+          const int q = mask_ffs(m) - 1;
+          const uint64_t e = G.L->ab[i * G.redraws + q];
+          const int c = (int)(uint32_t)e, j = (int)(uint32_t)(e >> 32);
+          if (grp_ballot(G, G.in(fixed) && val == c) == (Mask)0) {
+            if (G.sub == j) val = c;
+            fixed |= (Mask)1 << j;
+            open &= ~((Mask)1 << q);
+          }
+        }
+      pend &= ~fixed;
+    }
+    return val;
+  }
   for (uint32_t a = 0; pend != 0; ++a) {
     if (a >= 65536u) {   // acceptance probability is > 1/2 per draw: unreachable for a simple graph
       if (G.sub == 0) atomicOr(&state[ST_ERROR], ERR_REJECT_OVERFLOW);
       break;
     }
     const int np = mask_popc(pend);
-    if (GrpT<W>::POW2 && !FEW && np <= 8 && a + (uint32_t)GRP <= 65536u) {   // (the lane -> (slot, round) split below wants a power of two)
+    if (GrpT<W>::POW2 && np <= 8 && a + (uint32_t)GRP <= 65536u) {   // (the lane -> (slot, round) split below wants a power of two)
       // Few slots pending: a round would run the whole Philox block and a trip to the adjacency for a handful of
       // lanes.  Instead the 32 lanes compute the proposals of A = 16 / 8 / 4 consecutive rounds at once (lane ->
       // (pending slot q, round t); a proposal is a pure function of slot and round), and the rounds are then
@@ -244,26 +288,14 @@ __device__ __forceinline__ int grp_rejection_fill(const GrpT<W>& G, MaskT<W> pen
     int cand = -3;
     if (mine) cand = adj[below(lo64(draw_block(K, purpose, (uint32_t)G.sub, a)), deg)];
     bool reject = false;
-    if (FEW) {
-      const bool have = G.in(fixed);
-      if (mine) G.L->out[G.sub] = cand;
-      for (Mask m = pend; m != 0; m &= m - (Mask)1) {      // m is the same in all lanes of the group
-        const int j = mask_ffs(m) - 1;
-        const int cj = G.L->out[j];
-        const bool hit = (have && val == cj) || (mine && G.sub < j && cand == cj);
-        const bool taken = grp_ballot(G, hit) != (Mask)0;
-        if (G.sub == j) reject = taken;
-      }
-    } else {
-      if (G.sub < k) {
-        const int fx = G.in(fixed) ? val : -1;
-        G.L->ab[G.sub] = (uint64_t)(uint32_t)fx | ((uint64_t)(uint32_t)(mine ? cand : -2) << 32);
-      }
+    if (G.sub < k) {
+      const int fx = G.in(fixed) ? val : -1;
+      G.L->ab[G.sub] = (uint64_t)(uint32_t)fx | ((uint64_t)(uint32_t)(mine ? cand : -2) << 32);
+    }
 #pragma unroll 4
-      for (int i = 0; i < k; ++i) {
-        const uint64_t e = G.L->ab[i];
-        reject |= ((int)(uint32_t)e == cand) | (((int)(uint32_t)(e >> 32) == cand) & (i < G.sub));
-      }
+    for (int i = 0; i < k; ++i) {
+      const uint64_t e = G.L->ab[i];
+      reject |= ((int)(uint32_t)e == cand) | (((int)(uint32_t)(e >> 32) == cand) & (i < G.sub));
     }
     const bool acc = mine && !reject;
     if (acc) val = cand;
@@ -293,6 +325,39 @@ __device__ __forceinline__ void grp_select_positions(const GrpT<W>& G, int d, in
   if (s1) G.L->out[mask_popc(m0) + mask_popc(m1 & G.below())] = a1;
 }
 
+// The same where the ids of some slots are excluded (retained: lanes of `kept`, id in `val`): of the d positions at most
+// `want` more than k are eligible, so they usually fit the group's lanes when they are moved together: one Philox block and
+// one rank among the eligible ones instead of two blocks and two ranks among d.
+template <int W>
+__device__ __forceinline__ void grp_redraw_positions(const GrpT<W>& G, int d, int want, int k, MaskT<W> kept, int val,
+                                                     const int32_t* __restrict__ adj, const DrawKey& K, uint32_t purpose) {
+  bool e0 = G.sub < d, e1 = G.sub + W < d;
+  const int a0 = e0 ? adj[G.sub] : -1, a1 = e1 ? adj[G.sub + W] : -1;
+  if (G.sub < k) G.L->out[G.sub] = G.in(kept) ? val : -1;
+#pragma unroll 4
+  for (int j = 0; j < k; ++j) {
+    const int rv = G.L->out[j];
+    e0 &= (rv != a0);
+    e1 &= (rv != a1);
+  }
+  const MaskT<W> m0 = grp_ballot(G, e0), m1 = grp_ballot(G, e1);
+  const int n0 = mask_popc(m0), n = n0 + mask_popc(m1);
+  if (n > W) {
+    grp_select_positions(G, d, want, e0, e1, a0, a1, K, purpose);
+    return;
+  }
+  if (e0) G.L->ab[mask_popc(m0 & G.below())] = (uint64_t)(uint32_t)a0 | ((uint64_t)(uint32_t)G.sub << 32);
+  if (e1) G.L->ab[n0 + mask_popc(m1 & G.below())] = (uint64_t)(uint32_t)a1 | ((uint64_t)(uint32_t)(G.sub + W) << 32);
+  const uint64_t mine = G.L->ab[G.sub];
+  const uint32_t pos = (uint32_t)(mine >> 32);
+  uint64_t p = PRIO_NONE;
+  if (G.sub < n) p = priority(lo64(draw_block(K, purpose, pos, 0)), pos);
+  G.L->prio[G.sub] = p;
+  const bool sel = G.sub < n && grp_rank(G, n, p) < want;
+  const MaskT<W> m = grp_ballot(G, sel);
+  if (sel) G.L->out[mask_popc(m & G.below())] = (int)(uint32_t)mine;
+}
+
 // FILL_FULL for one row: returns the value of slot `sub` (-1 beyond the row).
 template <int W>
 __device__ __forceinline__ int grp_fill_full_row(const GrpT<W>& G, const int32_t* __restrict__ adj, uint32_t deg, int k,
@@ -317,7 +382,6 @@ template <int W>
 __device__ __forceinline__ int grp_refresh_part(const GrpT<W>& G, int val, int k, int n_new, const Block4& sb,
                                                 const int32_t* __restrict__ adj, uint32_t deg, const DrawKey& K,
                                                 int32_t* state, MaskT<W>& evict) {
-  constexpr int GRP = W;
   const int sub = G.sub;
   const MaskT<W> slots = GrpT<W>::first(k);
   const uint64_t e = (sub < k) ? priority(lo64(sb), (uint32_t)sub) : PRIO_NONE;
@@ -358,17 +422,7 @@ __device__ __forceinline__ int grp_refresh_part(const GrpT<W>& G, int val, int k
   const MaskT<W> retained = slots & ~evict;
   if (deg < 2u * (uint32_t)k) {
     // priority regime: a position is eligible unless its id sits in a retained slot
-    const int d = (int)deg;
-    bool e0 = sub < d, e1 = sub + GRP < d;
-    const int a0 = e0 ? adj[sub] : -1, a1 = e1 ? adj[sub + GRP] : -1;
-    if (sub < k) G.L->ab[sub] = (uint64_t)(uint32_t)(G.in(retained) ? val : -1);
-#pragma unroll 4
-    for (int j = 0; j < k; ++j) {
-      const int rv = (int)(uint32_t)G.L->ab[j];
-      e0 &= (rv != a0);
-      e1 &= (rv != a1);
-    }
-    grp_select_positions(G, d, n_new, e0, e1, a0, a1, K, P_FILL_PART);
+    grp_redraw_positions(G, (int)deg, n_new, k, retained, val, adj, K, P_FILL_PART);
     if (G.in(evict)) val = G.L->out[mask_popc(evict & G.below())];
   } else {
     val = grp_rejection_fill<true>(G, evict, retained, val, k, adj, deg, K, P_FILL_PART, state);
@@ -395,6 +449,7 @@ __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
   __shared__ int wave_heavy[4];
   GrpT<W> G;
   G.init(lds);
+  G.set_redraws(P.n_new);
   const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int sshift = (P.S == 64) ? 6 : (P.S == 32) ? 5 : 4;
   const int64_t nchunks = (P.n_dst + FILL_CHUNK - 1) / FILL_CHUNK;
@@ -460,6 +515,7 @@ __global__ __launch_bounds__(256) void fill_heavy_kernel(FillParams P, const int
   __shared__ GroupLdsT<W> lds[256 / W];
   GrpT<W> G;
   G.init(lds);
+  G.set_redraws(P.n_new);
   constexpr int GROUPS = 256 / W;
   const int sshift = (P.S == 64) ? 6 : (P.S == 32) ? 5 : 4;
   const int64_t items = nheavy * P.ntab;
@@ -657,10 +713,10 @@ __device__ __forceinline__ void sample_phase(const HP& P, const Wg wg, GroupLdsT
     return;
   }
   using Mask = MaskT<W>;
-  constexpr int GRP = W;
   GrpT<W> G;
   G.init(lds);
   if (G.idle) return;                 // (no barrier below: the phase is a per-group loop)
+  G.set_redraws(P.n_new);
   const int r = wg.y;
   const RelParam& RP = rel_of(P, r);
   const RelConst& RC = P.rc(r);
@@ -770,17 +826,7 @@ __device__ __forceinline__ void sample_phase(const HP& P, const Wg wg, GroupLdsT
       const int32_t* adj = RC.indices + b;
       const uint32_t deg = (uint32_t)d64;
       if (deg < 2u * (uint32_t)f) {
-        const int d = (int)deg;
-        bool e0 = sub < d, e1 = sub + GRP < d;
-        const int a0 = e0 ? adj[sub] : -1, a1 = e1 ? adj[sub + GRP] : -1;
-        if (sub < f) G.L->ab[sub] = (uint64_t)(uint32_t)(G.in(kept) ? cv : -1);
-#pragma unroll 4
-        for (int j = 0; j < f; ++j) {
-          const int rv = (int)(uint32_t)G.L->ab[j];
-          e0 &= (rv != a0);
-          e1 &= (rv != a1);
-        }
-        grp_select_positions(G, d, P.n_new, e0, e1, a0, a1, K, P_FETCH);
+        grp_redraw_positions(G, (int)deg, P.n_new, f, kept, cv, adj, K, P_FETCH);
         if (G.in(redraw)) cv = G.L->out[mask_popc(redraw & G.below())];
       } else {
         cv = grp_rejection_fill<true>(G, redraw, kept, cv, f, adj, deg, K, P_FETCH, P.state);
@@ -940,6 +986,7 @@ template <bool AHEAD, class HP>
 __device__ __forceinline__ void chain_phase(const HP& P, const ChainArgs& C, const Wg wg, GroupLds* lds, ChainLds* CL) {
   Grp G;
   G.init(lds);
+  G.set_redraws(P.n_new);
   const int c = P.hop, sub = G.sub, L = C.L;
   const int grp = wg.x * (int)(blockDim.x >> 5) + (int)(threadIdx.x >> 5);
   const int ngrp = P.gx * (int)(blockDim.x >> 5);
