@@ -21,6 +21,7 @@
 // missing ticks itself when fewer steps follow.  Host cost per step: one launch, which also completes the
 // finished step's event.
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -40,6 +41,7 @@ constexpr int TICK_EVENTS = 2 * GSS_MAX_IN_FLIGHT;   // more than the steps that
 constexpr int64_t SAMPLE_WIDE_GROUPS = 4096;      // expected frontier nodes of a hop from which a sample group takes two nodes (several relations)
 constexpr int64_t INSERT_SPLIT_SLOTS = 48 * 1024;   // expected pick slots of a hop from which its inserts get their own phase
 constexpr int64_t TWO_STEP_PICKS = 400 * 1024;    // expected picks of a step up to which two steps share a tick
+constexpr uint64_t DEEP_RING_BYTES = 192ull << 20;  // dedupe tables of a ring deep enough for two steps per tick
 constexpr int64_t NARROW_MIN_NODES = 16 * 1024;     // expected frontier nodes of a launch's sample slices from which they take narrow groups
 constexpr int64_t INSERT_SMALL_SLOTS = 16 * 1024;   // ... and up to which they do, too (narrow hops)
 constexpr double SETTLE_TYPED_TILES = 256.0;        // several relations: expected tiles of a hop up to which a blocking step settles it in one launch
@@ -169,7 +171,8 @@ struct Slot {
   uint32_t ver = VERSION_FIRST;          // next unused dedupe table version
   Buf src_nodes[GSS_MAX_LAYERS][GSS_MAX_NODE_TYPES];
   Buf src_local[GSS_MAX_LAYERS][GSS_MAX_RELATIONS], dst_local[GSS_MAX_LAYERS][GSS_MAX_RELATIONS];
-  hipEvent_t done = nullptr;             // completes when the step's last phase has run (the event of that tick, borrowed)
+  uint64_t done_launch = 0;              // number of the launch that holds the step's last phase
+  hipEvent_t done = nullptr;             // completes with that launch (borrowed from the kit), if it was issued for a waiting caller
   bool pending = false;                  // enqueued and not yet collected
   int L = 0, num_seeds = 0, seed_type = 0;
   // plan of the step the slot holds (host-known upper bounds of every hop)
@@ -278,6 +281,10 @@ struct gss_sampler {
   Slot slot[GSS_MAX_IN_FLIGHT];
   StepSizes largest;
   HopParams tick_all[2 * GSS_MAX_IN_FLIGHT], tick_launch[TICK_MAX_SLICES];   // scratch of tick(): slices of a tick, and of one launch
+  uint64_t launches = 0;                 // step launches so far (their numbers start at 1)
+  bool report_start = false;             // a step ended with the newest launch, which has no event: the next one reports its start
+  const volatile uint64_t* started_h = nullptr;   // pinned: number of the newest launch that has started, written by its first workgroup
+  uint64_t* started_dev = nullptr;
   int tick_ev_next = 0;                  // next of the kit's completion events (for the ticks in which steps finish, used round-robin)
   int steps_per_tick = 1, unlaunched = 0; // steps enqueued since the last tick
   bool waited = false;                   // the last call collected a step: a second one in a row means that the caller is draining
@@ -541,8 +548,12 @@ void fill_chain_slice(gss_sampler* s, Slot& sl, int c, HopParams& P) {
 // as the slice capacity allows.  Only sample phases depend on other steps:
 //   OTF         (t, h) after the sample phase of (t-1, h), issued in an EARLIER tick;
 //   SHARED_OTF  after every sample phase of step t-1.
-// Sets *issued to the number of phases put into the tick.
-gss_status tick(gss_sampler* s, int* issued) {
+// Sets *issued to the number of phases put into the tick.  `event`: which launches get a completion event - none; those with
+// which a step ends (the caller is about to wait for it); only the one after which no step has phases left.  (Otherwise the
+// next launch's start tells that this one is done: a launch that completes an event is followed by 4.5 us without a
+// wavefront - the fence to the host - against none, a third of a 1,024-seed FCR step.)
+enum TickEvent { EVENT_NEVER, EVENT_AT_STEP_END, EVENT_AT_LAST_END };
+gss_status tick(gss_sampler* s, int* issued, TickEvent event = EVENT_NEVER) {
   Slot* flight[GSS_MAX_IN_FLIGHT];
   const StepItems* items[GSS_MAX_IN_FLIGHT];
   int nf = 0;
@@ -578,7 +589,7 @@ gss_status tick(gss_sampler* s, int* issued) {
         for (int t = 0; t < s->T; ++t) mf = std::max(mf, (double)take[i]->fub[h][t]);
         nodes += std::min(1.0, 1.1 * (double)s->fill_ratio[h]) * mf;
       }
-    if (s->narrow_always || nodes >= (double)NARROW_MIN_NODES) width = s->narrow_w;
+    if (s->narrow_always || (nodes >= (double)NARROW_MIN_NODES && n <= 12)) width = s->narrow_w;
   }
   for (int i = 0; i < n; ++i) {
     if (pick[i].item >= 0) fill_slice(s, *take[i], pick[i].item, all[i], width);
@@ -591,17 +602,24 @@ gss_status tick(gss_sampler* s, int* issued) {
   auto rank_of = [&](int i) { return all[i].phase == PH_CHAIN ? -1 : weight(i); };
   std::sort(order, order + n, [&](int a, int b) { return rank_of(a) < rank_of(b); });
   // A step whose last phase (an emit phase, which writes its counts + error flag into pinned host memory) is in
-  // this tick is done when the tick's last launch is: that launch completes the step's `done` event itself.
-  // (Several steps may end with one tick: they share its event.)
+  // this tick is done when the tick's last launch is.  (Several steps may end with one tick: they share its event.)
   hipEvent_t done = nullptr;
+  bool ends = false;                     // a step ends with this tick
+  int left = 0;                          // phases that stay to be issued
+  for (int i = 0; i < nf; ++i) left += items[i]->num_items - items[i]->next_item + items[i]->num_chain - items[i]->next_chain;
+  const bool awaited = event == EVENT_AT_STEP_END || (event == EVENT_AT_LAST_END && left == n);
+  const int cap = width == 21 || width == 16 ? std::min(s->tick_cap, 12) : s->tick_cap;   // (the compact form has no narrow groups)
+  const uint64_t last_launch = s->launches + (uint64_t)((n + cap - 1) / cap);
   for (int i = 0; i < n; ++i)
     if (pick[i].item >= 0 && pick[i].item + 1 == take[i]->items.num_items) {
-      if (!done) { done = s->kit->tick_ev[s->tick_ev_next]; s->tick_ev_next = (s->tick_ev_next + 1) % TICK_EVENTS; }
+      ends = true;
+      if (!done && awaited) { done = s->kit->tick_ev[s->tick_ev_next]; s->tick_ev_next = (s->tick_ev_next + 1) % TICK_EVENTS; }
       take[i]->done = done;
+      take[i]->done_launch = last_launch;
     }
   s->unlaunched = 0;
-  for (int first = 0; first < n; first += s->tick_cap) {
-    const int m = std::min(n - first, s->tick_cap);
+  for (int first = 0; first < n; first += cap) {
+    const int m = std::min(n - first, cap);
     int wgs = 0;
     for (int i = 0; i < m; ++i) { P[i] = all[order[first + i]]; wgs += weight(order[first + i]); }
     const bool last = first + m == n;
@@ -610,8 +628,11 @@ gss_status tick(gss_sampler* s, int* issued) {
     // size, 1-4 % per step on the 1,024-seed workload; FBL and OTF fetch, which draw from the adjacency, lose 2-7 %)
     const bool rows_only = s->fcr && !s->shared && s->theta < 0;
     const bool dense = s->dense_policy == 1 || (s->dense_policy == 0 && (rows_only || wgs >= DENSE_TICK_WGS));
-    hipError_t e = launch_tick(P, m, s->relc_h, s->relc_d, s->slotc_d, s->visit_once, chain, s->work, s->timer, last ? done : nullptr, dense, width);
+    hipError_t e = launch_tick(P, m, s->relc_h, s->relc_d, s->slotc_d, s->visit_once, chain, LaunchMark{s->report_start ? s->started_dev : nullptr, s->launches + 1},
+                               s->work, s->timer, last ? done : nullptr, dense, width);
     if (e != hipSuccess) { s->poisoned = true; return fail(s, GSS_ERR_DEVICE, "launch: %s", hipGetErrorString(e)); }
+    ++s->launches;
+    s->report_start = last && ends && !done;
   }
   for (int i = 0; i < n; ++i) {
     if (pick[i].item >= 0) ++take[i]->items.next_item; else ++take[i]->items.next_chain;
@@ -626,11 +647,24 @@ gss_status drain(gss_sampler* s) {
     for (const Slot& sl : s->slot) open |= sl.pending && sl.items.open();
     if (!open) return GSS_OK;
     int issued = 0;
-    gss_status st = tick(s, &issued);
+    gss_status st = tick(s, &issued, EVENT_AT_LAST_END);
     if (st != GSS_OK) return st;
     // (the oldest step with phases left is always ready: the step before it has issued all of its own)
     if (issued == 0) { s->poisoned = true; return fail(s, GSS_ERR_DEVICE, "pipeline: no step is ready"); }
   }
+}
+
+// Waits until launch `number` has ended: the launch after it has started, or - if there is none, or it takes long - an event.
+hipError_t await_launch(gss_sampler* s, uint64_t number) {
+  if (s->launches > number)
+    for (int i = 0; i < 50000; ++i) {      // (a millisecond or two)
+      if (*s->started_h > number) { std::atomic_thread_fence(std::memory_order_acquire); return hipSuccess; }
+      __builtin_ia32_pause();
+    }
+  hipEvent_t ev = s->kit->tick_ev[s->tick_ev_next];
+  s->tick_ev_next = (s->tick_ev_next + 1) % TICK_EVENTS;
+  const hipError_t e = hipEventRecord(ev, s->work);
+  return e == hipSuccess ? hipEventSynchronize(ev) : e;
 }
 
 // Rewrite the tables of `set` for the epoch that starts at step `stepword` on the fill stream: after everything
@@ -806,10 +840,14 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
   hipError_t e = hipSuccess;
   // Modes whose sample phases write no table have no dependency between steps: a tick can start two of them,
   // which halves the launches and the idle time between them per step, where a launch has the slices for it
-  // (one-relation graphs: the compact form carries 24).  Measured on the 1,024-seed workload: FBL and OTF fetch
-  // -15 % per step; the epoch-refreshed modes gain nothing (their refresh kernel shares the chip with launches
-  // twice as large) and keep one step per tick.
-  s->steps_per_tick = (!s->otf && !s->fcr && s->R == 1 && s->T == 1 && s->k <= 32) ? 2 : 1;
+  // (one-relation graphs: the compact form carries 24).  Measured on the 1,024-seed workloads: FBL and OTF fetch
+  // -15 % per step, FCR on the 169k-node graph -8 %.  The ring is then twice as deep, and in
+  // the epoch-refreshed modes that can cost more than it saves: on the 2.4M-node graph the dedupe tables of 28 slots are more
+  // than the last-level cache holds (FCR +5 %; FBL and fetch still gain 4-20 % there), and with a short refresh period the
+  // steps of a deep ring span more epochs than there are table sets (period 5: +10 %).
+  const int deep = std::min(GSS_MAX_IN_FLIGHT, 2 * (4 * s->L + 2));
+  const bool deep_fits = !s->fcr || ((uint64_t)total_nodes * 8ull * (uint64_t)deep <= DEEP_RING_BYTES && deep / s->period <= MAX_TABLE_SETS - 1);
+  s->steps_per_tick = (!s->otf && s->R == 1 && s->T == 1 && s->k <= 32 && deep_fits) ? 2 : 1;
   if (tn.steps_per_tick) s->steps_per_tick = (!s->otf && s->k <= 32 && tn.steps_per_tick == 2) ? 2 : 1;
   if (s->lds_stage) s->steps_per_tick = 1;
   // Lanes per frontier node in the sample phase.  A row of k slots keeps k lanes busy, and a wavefront's vector
@@ -819,10 +857,9 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
   // of up to 12 slices only).
   s->group_w = s->k > 32 ? 64 : 32;
   const bool rows_mode = c->mode == GSS_MODE_FCR || c->mode == GSS_MODE_OTF || c->mode == GSS_MODE_OTF_LAYER || c->mode == GSS_MODE_SHARED_FCR;
-  if (s->k <= 20 && s->R == 1 && s->T == 1 && rows_mode && s->steps_per_tick == 1 && !s->lds_stage && !s->visit_once && tn.group_width != 32) {
+  if (s->k <= 20 && s->R == 1 && s->T == 1 && rows_mode && !s->lds_stage && !s->visit_once && tn.group_width != 32) {
     s->narrow_w = s->k <= 16 ? 16 : 21;
     s->narrow_always = tn.group_width == 1;
-    s->tick_cap = std::min(s->tick_cap, 12);
   }
   // A step of L hops has up to 4 L phases, one per launch: with two more steps than that in flight the step a
   // caller waits for has left the queue before.  (Deeper rings only widen the memory the launches touch: every slot
@@ -835,13 +872,15 @@ gss_status gss_create_tuned(const gss_graph* g, const gss_config* c, const gss_t
   if (tn.pipeline_depth) s->ring = tn.pipeline_depth;
   // ---- device states and their pinned host copies, 256 bytes apart: create-time, fill stream, one per slot of the ring ----
   const size_t stride = (sizeof(int32_t) * (size_t)s->state_words + 255) / 256 * 256, words = stride / sizeof(int32_t);
-  const size_t state_bytes = stride * (size_t)(s->ring + 2);
+  const size_t state_bytes = stride * (size_t)(s->ring + 2), pinned_bytes = state_bytes + 256;
   s->states_d = (int32_t*)dev_alloc(s, state_bytes);
   if (!s->states_d) return bail(GSS_ERR_OOM);
-  if ((e = take_kit(state_bytes, &s->kit)) != hipSuccess) return hipfail(e);
+  if ((e = take_kit(pinned_bytes, &s->kit)) != hipSuccess) return hipfail(e);
   s->work = s->kit->work;
   s->user_ready = s->kit->user_ready; s->fill_go = s->kit->fill_go; s->fill_done = s->kit->fill_done;
-  memset(s->kit->pinned, 0, state_bytes);
+  memset(s->kit->pinned, 0, pinned_bytes);
+  s->started_h = (const volatile uint64_t*)(s->kit->pinned + state_bytes);
+  s->started_dev = (uint64_t*)(s->kit->pinned_dev + state_bytes);
   int32_t* const pinned = (int32_t*)s->kit->pinned;
   s->state_d = s->states_d; s->state_h = pinned;
   s->fill_state_d = s->states_d + words; s->fill_state_h = pinned + words;
@@ -1285,19 +1324,19 @@ gss_status gss_step_wait(gss_sampler* s, gss_blocks* out) {
   // A second wait in a row: no steps follow for now (the end of an epoch), and every step in flight will be asked for.  All
   // their launches are issued at once - issued by the waits, one each, every launch of the drain came a round trip to the
   // host after the one before (30-40 us apart on the 1,024-seed workloads: a third of a pass of 40 steps).
-  if (s->waited && sl.items.open()) {
+  if (s->waited) {
     gss_status ds = drain(s);
     if (ds != GSS_OK) return ds;
   }
   s->waited = true;
   while (sl.items.open()) {  // fewer steps followed this one than it has phases
     int issued = 0;                      // (the oldest step in flight is always ready)
-    gss_status ms = tick(s, &issued);
+    gss_status ms = tick(s, &issued, EVENT_AT_STEP_END);
     if (ms != GSS_OK) return ms;
     if (issued == 0) { s->poisoned = true; return fail(s, GSS_ERR_DEVICE, "pipeline: the oldest step is not ready"); }
   }
   sl.pending = false;
-  hipError_t e = hipEventSynchronize(sl.done);
+  hipError_t e = sl.done ? hipEventSynchronize(sl.done) : await_launch(s, sl.done_launch);
   if (e != hipSuccess) { s->poisoned = true; return fail(s, GSS_ERR_DEVICE, "step_wait: %s", hipGetErrorString(e)); }
   const int32_t flag = sl.state_h[ST_ERROR];
   if (flag != 0) {

@@ -176,10 +176,18 @@ struct HopParamsStaged : HopParamsMono {};    // the same slice in the build who
 struct HopParamsChain : HopParamsStaged {};   // ... and in launches that also carry a chain's arguments
 template <class HP> struct ChainOf { static constexpr bool HAS_CHAIN = false; };
 template <> struct ChainOf<HopParamsChain> { static constexpr bool HAS_CHAIN = true; ChainArgs chain; };
+// The number of a launch, written to a word of pinned host memory when it starts: everything the launches before it on the
+// stream have done is then complete and visible on the GPU.  started == null: nobody waits for them (the launch would end
+// only when the write has reached the host: blocking steps +5 %).
+struct LaunchMark {
+  uint64_t* started;
+  uint64_t number;
+};
 template <class HP, int D>
 struct TickT : ChainOf<HP> {
   using Slice = HP;
   static constexpr int SLICES = D;
+  LaunchMark mark;
   HP s[D];
   int32_t end[D];           // running total of the slices' workgroups: slice i owns [end[i-1], end[i])
 };
@@ -223,6 +231,7 @@ struct MonoSlice {
 template <int D>
 struct TickMono {
   static constexpr int SLICES = D;
+  LaunchMark mark;
   MonoShared h;
   MonoSlice s[D];
   int32_t end[D];
@@ -266,9 +275,10 @@ hipError_t launch_list_from_map(const int32_t* map, int64_t n, int32_t* list, hi
 // `width`: lanes per frontier node in the sample phase - 64 for rows of more than 32 slots, 32, or (one-relation graphs,
 // at most 12 slices, no chain, no LDS stage) 21 / 16 for rows of up to 20 / 16 slots; the grids of the sample slices must
 // have been sized for it (256 / 64 * (64 / width) nodes per workgroup).
+// `mark`: written when the launch starts.
 hipError_t launch_tick(const HopParams* slices, int n, const RelConst* relc_host, const RelConst* relc_dev,
-                       const SlotConst* slots_dev, bool chain_build, const ChainArgs* chain, hipStream_t st, LaunchTimer* timer,
-                       hipEvent_t done, bool dense, int width);
+                       const SlotConst* slots_dev, bool chain_build, const ChainArgs* chain, const LaunchMark& mark, hipStream_t st,
+                       LaunchTimer* timer, hipEvent_t done, bool dense, int width);
 hipError_t launch_validate_graph(const void* indptr, int is64, int64_t n_dst, const int32_t* indices, int64_t nnz,
                                  int64_t n_src, int32_t* state, hipStream_t st);
 hipError_t launch_cache_read(const int32_t* table, const int32_t* row_of, int64_t n, int k, int S, int32_t* out,

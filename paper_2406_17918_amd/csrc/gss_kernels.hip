@@ -1825,6 +1825,9 @@ __device__ __forceinline__ void run_slice(const HP& P, int block, const ChainArg
       break;
   }
 }
+__device__ __forceinline__ void report_start(const LaunchMark& m) {
+  if (m.started && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(m.started, m.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 template <class TP, int W, bool DENSE = false>
 __device__ __forceinline__ void tick_body(const TP& M_by_value) {
   // The builds that carry a chain's arguments read their arguments where the launch put them, in the kernel argument
@@ -1836,6 +1839,7 @@ __device__ __forceinline__ void tick_body(const TP& M_by_value) {
   int z = 0;
 #pragma unroll
   for (int i = 0; i < TP::SLICES - 1; ++i) z += ((int)blockIdx.x >= M.end[i]) ? 1 : 0;
+  report_start(M.mark);                  // (not first: its argument then travels with the bounds)
   const ChainArgs* chain = nullptr;
   if constexpr (TP::HAS_CHAIN) chain = &M.chain;
   run_slice<W, DENSE>(M.s[z], (int)blockIdx.x - (z ? M.end[z - 1] : 0), chain);
@@ -1859,9 +1863,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(96))) void step
 #pragma unroll
   for (int i = 0; i < D - 1; ++i) z += ((int)blockIdx.x >= M.end[i]) ? 1 : 0;
   const MonoSlice& c = M.s[z];
-  const SlotConst& sc = M.h.slots[c.slot];
+  report_start(M.mark);
+  // (constant address space: scalar loads.  Entries only change between launches.)
+  const __attribute__((address_space(4))) SlotConst& sc = ((const __attribute__((address_space(4))) SlotConst*)(uintptr_t)M.h.slots)[c.slot];
   HopParamsMonoRegs H;
-  H.ht = sc.ht;
+  H.ht.direct = sc.ht.direct; H.ht.entries = sc.ht.entries; H.ht.mask = sc.ht.mask;
   H.state = sc.state;
   H.state_host = c.publish ? sc.state_host : nullptr;
   H.picks = sc.picks; H.order = sc.order; H.tile_off = sc.tile_off;
@@ -2148,11 +2154,12 @@ int tick_capacity(int R, int T) {
 
 template <class HP, int D>
 static hipError_t launch_tick_t(const HopParams* P, int n, const RelConst* relc_host, const RelConst* relc_dev,
-                                const ChainArgs* chain, hipStream_t st, LaunchTimer* timer, hipEvent_t done, bool dense,
-                                int width = 0) {
+                                const ChainArgs* chain, const LaunchMark& mark, hipStream_t st, LaunchTimer* timer,
+                                hipEvent_t done, bool dense, int width = 0) {
   using TP = TickT<HP, D>;
   static_assert(sizeof(TP) <= 4000, "kernel arguments are limited to 4 KB");
   TP M;
+  M.mark = mark;
   if constexpr (TP::HAS_CHAIN) {
     if (chain) M.chain = *chain; else memset(static_cast<void*>(&M.chain), 0, sizeof M.chain);
   } else if (chain) {
@@ -2203,11 +2210,12 @@ static hipError_t launch_tick_t(const HopParams* P, int n, const RelConst* relc_
 
 // The compact launch: slices of one-relation graphs, up to TICK_MONO_SLICES of them.
 static hipError_t launch_tick_mono(const HopParams* P, int n, const RelConst* relc_host, const SlotConst* slots_dev,
-                                   hipStream_t st, LaunchTimer* timer, hipEvent_t done) {
+                                   const LaunchMark& mark, hipStream_t st, LaunchTimer* timer, hipEvent_t done) {
   using TM = TickMono<TICK_MONO_SLICES>;
   static_assert(sizeof(TM) <= 4000, "kernel arguments are limited to 4 KB");
   TM M;
   memset(static_cast<void*>(&M), 0, sizeof M);
+  M.mark = mark;
   const HopParams& A = P[0];
   M.h.relc = relc_host[0];
   M.h.slots = slots_dev;
@@ -2248,42 +2256,42 @@ static hipError_t launch_tick_mono(const HopParams* P, int n, const RelConst* re
 }
 
 hipError_t launch_tick(const HopParams* P, int n, const RelConst* relc_host, const RelConst* relc_dev,
-                       const SlotConst* slots_dev, bool chain_build, const ChainArgs* chain, hipStream_t st, LaunchTimer* timer,
-                       hipEvent_t done, bool dense, int width) {
+                       const SlotConst* slots_dev, bool chain_build, const ChainArgs* chain, const LaunchMark& mark, hipStream_t st,
+                       LaunchTimer* timer, hipEvent_t done, bool dense, int width) {
   if (n < 1 || n > tick_capacity(P[0].R, P[0].T)) return hipErrorInvalidValue;
   const int R = P[0].R, T = P[0].T;
   if (chain_build) {
     if (R != 1 || T != 1 || n > CHAIN_TICK_SLICES) return hipErrorInvalidValue;
-    if (n <= 4) return launch_tick_t<HopParamsChain, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-    return launch_tick_t<HopParamsChain, CHAIN_TICK_SLICES>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
+    if (n <= 4) return launch_tick_t<HopParamsChain, 4>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
+    return launch_tick_t<HopParamsChain, CHAIN_TICK_SLICES>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
   }
   if (chain) return hipErrorInvalidValue;
   if (P[0].insert_split & 2) {      // the sampler uses the LDS stage of the dedupe: a build of its own (one relation, rows of up to 32 slots)
     if (R != 1 || T != 1 || n > 12 || P[0].k > 32) return hipErrorInvalidValue;
-    return launch_tick_t<HopParamsStaged, 12>(P, n, relc_host, relc_dev, nullptr, st, timer, done, dense);
+    return launch_tick_t<HopParamsStaged, 12>(P, n, relc_host, relc_dev, nullptr, mark, st, timer, done, dense);
   }
   const bool narrow = width == 21 || width == 16;
   if (narrow && (chain_build || (P[0].insert_split & 2) || R != 1 || T != 1 || n > 12)) return hipErrorInvalidValue;
   if (R == 1 && T == 1 && n > 12) {
     if (!slots_dev || P[0].k > 32) return hipErrorInvalidValue;   // (the compact form has no build for wide rows)
-    return launch_tick_mono(P, n, relc_host, slots_dev, st, timer, done);
+    return launch_tick_mono(P, n, relc_host, slots_dev, mark, st, timer, done);
   }
   if (R == 1 && T == 1) {
-    if (n <= 4) return launch_tick_t<HopParamsMono, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
-    if (n <= 8) return launch_tick_t<HopParamsMono, 8>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
-    return launch_tick_t<HopParamsMono, 12>(P, n, relc_host, relc_dev, chain, st, timer, done, dense, width);
+    if (n <= 4) return launch_tick_t<HopParamsMono, 4>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense, width);
+    if (n <= 8) return launch_tick_t<HopParamsMono, 8>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense, width);
+    return launch_tick_t<HopParamsMono, 12>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense, width);
   }
   if (R <= HopParamsSmall::MAX_R && T <= HopParamsSmall::MAX_T) {
-    if (n <= 3) return launch_tick_t<HopParamsSmall, 3>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-    if (n <= 6) return launch_tick_t<HopParamsSmall, 6>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-    return launch_tick_t<HopParamsSmall, 9>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
+    if (n <= 3) return launch_tick_t<HopParamsSmall, 3>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
+    if (n <= 6) return launch_tick_t<HopParamsSmall, 6>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
+    return launch_tick_t<HopParamsSmall, 9>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
   }
   if (R <= HopParamsMid::MAX_R && T <= HopParamsMid::MAX_T) {
-    if (n <= 3) return launch_tick_t<HopParamsMid, 3>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-    return launch_tick_t<HopParamsMid, 6>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
+    if (n <= 3) return launch_tick_t<HopParamsMid, 3>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
+    return launch_tick_t<HopParamsMid, 6>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
   }
-  if (n <= 2) return launch_tick_t<HopParams, 2>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
-  return launch_tick_t<HopParams, 4>(P, n, relc_host, relc_dev, chain, st, timer, done, dense);
+  if (n <= 2) return launch_tick_t<HopParams, 2>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
+  return launch_tick_t<HopParams, 4>(P, n, relc_host, relc_dev, chain, mark, st, timer, done, dense);
 }
 
 hipError_t launch_validate_graph(const void* indptr, int is64, int64_t n_dst, const int32_t* indices, int64_t nnz,
