@@ -145,6 +145,15 @@ struct GrpT {
   __device__ __forceinline__ Mask below() const { return ((Mask)1 << sub) - (Mask)1; }          // the lanes before this one
   __device__ __forceinline__ bool in(Mask m) const { return ((m >> sub) & (Mask)1) != 0; }       // is this lane's bit set
   __device__ __forceinline__ static Mask all() { return (W == 64 || W == 32) ? ~(Mask)0 : (Mask)(((Mask)1 << (W & 31)) - (Mask)1); }
+  // the lanes of the wavefront that come after lane i of their group
+  __device__ __forceinline__ static uint64_t wave_lanes_after(int i) {
+    const uint64_t one = (uint64_t)all() & ~(((uint64_t)2 << i) - 1ull);
+    if constexpr (W == 64) return one;
+    uint64_t m = 0ull;
+#pragma unroll
+    for (int q = 0; q < PER_WAVE; ++q) m |= one << (q * W);
+    return m;
+  }
   __device__ __forceinline__ static Mask first(int n) { return n >= W ? all() : (((Mask)1 << n) - (Mask)1); }
 };
 using GroupLds = GroupLdsT<32>;
@@ -194,6 +203,27 @@ __device__ __forceinline__ void grp_rank2(const GrpT<W>& G, int n, uint64_t p0, 
   }
 }
 
+// Takes the proposals of n pending slots in order, attempt by attempt and slot by slot: lane `i * stride + q` holds the
+// proposal `cand` of attempt i < drawn for pending slot number q, which is slot `slot` of the row.  A slot is fixed to its first
+// proposal that no fixed slot holds.
+template <int W>
+__device__ __forceinline__ void take_in_order(const GrpT<W>& G, int cand, int slot, int n, int stride, int drawn, MaskT<W>& fixed, int& val) {
+  using Mask = MaskT<W>;
+  G.L->ab[G.sub] = (uint64_t)(uint32_t)cand | ((uint64_t)(uint32_t)slot << 32);
+  Mask open = GrpT<W>::first(n);                                          // pending, by number
+  for (int i = 0; i < drawn && open != 0; ++i)
+    for (Mask m = open; m != 0; m &= m - (Mask)1) {                       // (the same in all lanes of the group)
+      const int q = mask_ffs(m) - 1;
+      const uint64_t e = G.L->ab[i * stride + q];
+      const int c = (int)(uint32_t)e, j = (int)(uint32_t)(e >> 32);
+      if (grp_ballot(G, G.in(fixed) && val == c) == (Mask)0) {
+        if (G.sub == j) val = c;
+        fixed |= (Mask)1 << j;
+        open &= ~((Mask)1 << q);
+      }
+    }
+}
+
 // Round-major rejection fill.  Slots of `pend` need an id, slots of `fixed` hold one in `val`.
 // In round a every pending slot j draws pos = below(deg; index=j, attempt=a) and proposes
 // adj[pos]; it is accepted unless the id is already in the row or proposed by a lower pending slot
@@ -205,12 +235,11 @@ __device__ __forceinline__ void grp_rank2(const GrpT<W>& G, int n, uint64_t p0, 
 // half of the wavefronts needed one or more).  Up to four attempts where a repeat is likely and the adjacency is a few
 // cache lines (deg < 8 k), two up to deg < 32 k; the neighbors of a hub lie in a line each, and there one attempt nearly
 // always does.
-// From eight pending slots down, the fill of a whole row draws several rounds at once (below).
+// The fill of a whole row (FEW = false: every slot pending) does the same from its second round on.
 template <bool FEW, int W>
 __device__ __forceinline__ int grp_rejection_fill(const GrpT<W>& G, MaskT<W> pend, MaskT<W> fixed, int val, int k,
                                                   const int32_t* __restrict__ adj, uint32_t deg,
                                                   const DrawKey& K, uint32_t purpose, int32_t* state) {
-  using Mask = MaskT<W>;
   constexpr int GRP = W;
   if constexpr (FEW) {
     const int most = deg < 8u * (uint32_t)k ? 4 : (deg < 32u * (uint32_t)k ? 2 : 1);
@@ -225,83 +254,41 @@ __device__ __forceinline__ int grp_rejection_fill(const GrpT<W>& G, MaskT<W> pen
       const int slot = G.L->out[my_q];
       int cand = -3;
       if (my_a < drawn && my_q < n) cand = adj[below(lo64(draw_block(K, purpose, (uint32_t)slot, a + (uint32_t)my_a)), deg)];
-      G.L->ab[G.sub] = (uint64_t)(uint32_t)cand | ((uint64_t)(uint32_t)slot << 32);
-      Mask open = GrpT<W>::first(n);                                      // pending, by number
-      for (int i = 0; i < drawn && open != 0; ++i)
-        for (Mask m = open; m != 0; m &= m - (Mask)1) {                   // (the same in all lanes of the group)
-          const int q = mask_ffs(m) - 1;
-          const uint64_t e = G.L->ab[i * G.redraws + q];
-          const int c = (int)(uint32_t)e, j = (int)(uint32_t)(e >> 32);
-          if (grp_ballot(G, G.in(fixed) && val == c) == (Mask)0) {
-            if (G.sub == j) val = c;
-            fixed |= (Mask)1 << j;
-            open &= ~((Mask)1 << q);
-          }
-        }
+      take_in_order(G, cand, slot, n, G.redraws, drawn, fixed, val);
       pend &= ~fixed;
     }
     return val;
   }
-  for (uint32_t a = 0; pend != 0; ++a) {
-    if (a >= 65536u) {   // acceptance probability is > 1/2 per draw: unreachable for a simple graph
+  // A whole row (nothing is fixed yet).  First round: a slot only has to differ from the lower slots' proposals, and the
+  // comparisons are collected as wavefront masks (one vector instruction per slot).
+  const bool in_row = G.sub < k;
+  int cand = in_row ? adj[below(lo64(draw_block(K, purpose, (uint32_t)G.sub, 0)), deg)] : -3;
+  G.L->out[G.sub] = cand;
+  uint64_t taken = 0ull;
+#pragma unroll 4
+  for (int i = 0; i < k; ++i) taken |= __ballot(G.L->out[i] == cand) & GrpT<W>::wave_lanes_after(i);
+  const bool acc = in_row && !((taken >> lane_id()) & 1ull);
+  if (acc) val = cand;
+  fixed = grp_ballot(G, acc);
+  pend &= ~fixed;
+  for (uint32_t a = 1; pend != 0;) {
+    if (a >= 65536u - (uint32_t)GRP) {   // acceptance probability is > 1/2 per draw: unreachable for a simple graph
       if (G.sub == 0) atomicOr(&state[ST_ERROR], ERR_REJECT_OVERFLOW);
       break;
     }
-    const int np = mask_popc(pend);
-    if (GrpT<W>::POW2 && np <= 8 && a + (uint32_t)GRP <= 65536u) {   // (the lane -> (slot, round) split below wants a power of two)
-      // Few slots pending: a round would run the whole Philox block and a trip to the adjacency for a handful of
-      // lanes.  Instead the 32 lanes compute the proposals of A = 16 / 8 / 4 consecutive rounds at once (lane ->
-      // (pending slot q, round t); a proposal is a pure function of slot and round), and the rounds are then
-      // resolved in order from LDS: same outcome, one block and one trip for all of them.
-      const int lg = np <= 2 ? 1 : (np <= 4 ? 2 : 3);
-      const int A = GRP >> lg;
-      const int q = G.sub >> (GrpT<W>::LOG2_WIDTH - lg), t = G.sub & (A - 1);
-      Mask m = pend;
-      for (int i = 0; i < q; ++i) m &= m - (Mask)1;                  // drop the q lowest pending slots
-      const int jq = (q < np) ? mask_ffs(m) - 1 : -1;                // slot of pending index q
-      int c = -3;
-      if (jq >= 0) c = adj[below(lo64(draw_block(K, purpose, (uint32_t)jq, a + (uint32_t)t)), deg)];
-      G.L->out[G.sub] = c;                                           // proposal of (q, t) at q * A + t
-      const bool mine0 = G.in(pend);
-      const int my_q = mask_popc(pend & G.below());                  // pending index of the lane's own slot
-      uint32_t pm = (1u << np) - 1u;                                 // pending, by pending index
-      for (int tt = 0; tt < A && pm != 0u; ++tt) {
-        const bool have = G.in(fixed);
-        uint32_t acc = 0u;
-        for (uint32_t w = pm; w != 0u; w &= w - 1u) {               // (w is the same in all lanes of the group)
-          const int qq = __ffs((int)w) - 1;
-          const int cj = G.L->out[qq * A + tt];
-          // lane l < np stands for the pending slot of index l: a lower pending slot with the same proposal
-          const bool lower = G.sub < qq && ((pm >> G.sub) & 1u) && G.L->out[G.sub * A + tt] == cj;
-          if (grp_ballot(G, (have && val == cj) || lower) == (Mask)0) acc |= 1u << qq;
-        }
-        const bool got = mine0 && ((acc >> my_q) & 1u);
-        if (got) val = G.L->out[my_q * A + tt];
-        fixed |= grp_ballot(G, got);
-        pm &= ~acc;
-      }
-      pend = grp_ballot(G, mine0 && ((pm >> my_q) & 1u));
-      a += (uint32_t)A - 1u;
-      continue;
-    }
-    const bool mine = G.in(pend);
-    int cand = -3;
-    if (mine) cand = adj[below(lo64(draw_block(K, purpose, (uint32_t)G.sub, a)), deg)];
-    bool reject = false;
-    if (G.sub < k) {
-      const int fx = G.in(fixed) ? val : -1;
-      G.L->ab[G.sub] = (uint64_t)(uint32_t)fx | ((uint64_t)(uint32_t)(mine ? cand : -2) << 32);
-    }
-#pragma unroll 4
-    for (int i = 0; i < k; ++i) {
-      const uint64_t e = G.L->ab[i];
-      reject |= ((int)(uint32_t)e == cand) | (((int)(uint32_t)(e >> 32) == cand) & (i < G.sub));
-    }
-    const bool acc = mine && !reject;
-    if (acc) val = cand;
-    const Mask accm = grp_ballot(G, acc);
-    pend &= ~accm;
-    fixed |= accm;
+    // The slots left are few: a round would run the whole Philox block and a trip to the adjacency for a handful of lanes.
+    // Instead the lanes draw the slots' next GRP / n attempts at once (lane = attempt * n + number of the pending slot; a
+    // proposal is a pure function of slot and attempt), which are then taken in order from LDS.
+    const int n = mask_popc(pend);
+    if (G.in(pend)) G.L->out[mask_popc(pend & G.below())] = G.sub;
+    const float inv = __builtin_amdgcn_rcpf((float)n);                    // (sub + 1/2) / n is never near a whole number
+    const int my_a = (int)(((float)G.sub + 0.5f) * inv), my_q = G.sub - my_a * n, drawn = (int)(((float)GRP + 0.5f) * inv);
+    const int slot = G.L->out[my_q];
+    cand = -3;
+    if (my_a < drawn) cand = adj[below(lo64(draw_block(K, purpose, (uint32_t)slot, a + (uint32_t)my_a)), deg)];
+    take_in_order(G, cand, slot, n, n, drawn, fixed, val);
+    pend &= ~fixed;
+    a += (uint32_t)drawn;
   }
   return val;
 }
@@ -438,10 +425,16 @@ __device__ __forceinline__ int grp_refresh_part(const GrpT<W>& G, int val, int k
 //   C  the flagged rows are compacted into a list, and (row, table) pairs are dealt to the eight
 //      32-lane groups, so both halves of every wavefront run the Philox / rejection code together.
 // ------------------------------------------------------------------------------------------
+// A row of S slots: value `val` of slot `sub`, -1 in the slots beyond the group's lanes.
+template <int W>
+__device__ __forceinline__ void store_row(int32_t* row, int sub, int S, int val) {
+  if (sub < S) row[sub] = val;
+  if (W < 32 && sub + W < S) row[sub + W] = -1;
+}
 constexpr int FILL_CHUNK = 64;    // rows per chunk: small enough that a few thousand workgroups share the rejection work
 template <int W>
 __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
-  __shared__ GroupLdsT<W> lds[256 / W];
+  __shared__ GroupLdsT<W> lds[GrpT<W>::PER_WG];
   __shared__ long long row_base[FILL_CHUNK];
   __shared__ int row_deg[FILL_CHUNK];
   __shared__ int row_at[FILL_CHUNK];          // table row of the node, -1: the node keeps no row (degree split)
@@ -486,7 +479,7 @@ __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
     __syncthreads();
     // ---- C: heavy rows, one W-lane group per (row, table) ----
     const int items = nheavy * P.ntab;
-    for (int it = tid / W; it < items; it += 256 / W) {
+    for (int it = G.idle ? items : G.index_in_workgroup(); it < items; it += GrpT<W>::PER_WG) {
       const int row = heavy_rows[it / P.ntab], t = it % P.ntab;
       const int64_t v = v0 + row;
       DrawKey K{P.seed_lo, P.seed_hi, (uint32_t)v, P.stepword, (P.layer_word[t] << 8) | (P.relation << 16)};
@@ -501,7 +494,7 @@ __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
       } else {
         val = grp_fill_full_row(G, P.indices + row_base[row], (uint32_t)row_deg[row], P.k, K, P_FILL_FULL, P.state);
       }
-      if (G.sub < P.S) P.table[t][((int64_t)row_at[row] << sshift) + G.sub] = val;
+      store_row<W>(P.table[t] + ((int64_t)row_at[row] << sshift), G.sub, P.S, val);
     }
     __syncthreads();
   }
@@ -512,14 +505,15 @@ __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
 // with more (a list made once at set-up): one 32-lane group per (row, table), no chunk staging, no barriers.
 template <int W>
 __global__ __launch_bounds__(256) void fill_heavy_kernel(FillParams P, const int32_t* __restrict__ heavy, int64_t nheavy) {
-  __shared__ GroupLdsT<W> lds[256 / W];
+  __shared__ GroupLdsT<W> lds[GrpT<W>::PER_WG];
   GrpT<W> G;
   G.init(lds);
+  if (G.idle) return;
   G.set_redraws(P.n_new);
-  constexpr int GROUPS = 256 / W;
+  constexpr int GROUPS = GrpT<W>::PER_WG;
   const int sshift = (P.S == 64) ? 6 : (P.S == 32) ? 5 : 4;
   const int64_t items = nheavy * P.ntab;
-  for (int64_t it = (int64_t)blockIdx.x * GROUPS + (int64_t)(threadIdx.x / W); it < items; it += (int64_t)gridDim.x * GROUPS) {
+  for (int64_t it = (int64_t)blockIdx.x * GROUPS + G.index_in_workgroup(); it < items; it += (int64_t)gridDim.x * GROUPS) {
     const int64_t v = heavy[it / P.ntab];
     const int t = (int)(it % P.ntab);
     const int64_t b = load_indptr(P.indptr, P.is64, v);
@@ -536,7 +530,7 @@ __global__ __launch_bounds__(256) void fill_heavy_kernel(FillParams P, const int
     } else {
       val = grp_fill_full_row(G, P.indices + b, deg, P.k, K, P_FILL_FULL, P.state);
     }
-    if (G.sub < P.S) P.table[t][at + G.sub] = val;
+    store_row<W>(P.table[t] + at, G.sub, P.S, val);
   }
 }
 
@@ -2118,7 +2112,8 @@ static inline unsigned clamp_grid(int64_t want, int64_t cap) {
 hipError_t launch_fill_full(const FillParams& P, hipStream_t st, LaunchTimer* timer) {
   const unsigned grid = clamp_grid((P.n_dst + FILL_CHUNK - 1) / FILL_CHUNK, 8192);
   hipEvent_t start = nullptr, stop = nullptr;
-  void (*const kernel)(FillParams) = P.k > 32 ? fill_full_kernel<64> : fill_full_kernel<32>;   // rows wider than half a wavefront
+  void (*const kernel)(FillParams) = P.k > 32 ? fill_full_kernel<64> : P.k > 20 ? fill_full_kernel<32> : P.k > 16 ? fill_full_kernel<21>
+                                                                     : fill_full_kernel<16>;   // lanes per heavy row
   if (timer && timer->bracket(KID_FILL_FULL, &start, &stop))      // the events get the dispatch's own start / end times
     hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, start, stop, 0, P);
   else
@@ -2128,10 +2123,11 @@ hipError_t launch_fill_full(const FillParams& P, hipStream_t st, LaunchTimer* ti
 
 hipError_t launch_fill_heavy(const FillParams& P, const int32_t* heavy, int64_t nheavy, hipStream_t st, LaunchTimer* timer) {
   if (nheavy <= 0) return hipSuccess;
-  const int groups = P.k > 32 ? 4 : 8;
+  const int groups = P.k > 32 ? 4 : P.k > 20 ? 8 : P.k > 16 ? 12 : 16;
   const unsigned grid = clamp_grid((nheavy * P.ntab + groups - 1) / groups, 16384);
   hipEvent_t start = nullptr, stop = nullptr;
-  void (*const kernel)(FillParams, const int32_t*, int64_t) = P.k > 32 ? fill_heavy_kernel<64> : fill_heavy_kernel<32>;
+  void (*const kernel)(FillParams, const int32_t*, int64_t) =
+      P.k > 32 ? fill_heavy_kernel<64> : P.k > 20 ? fill_heavy_kernel<32> : P.k > 16 ? fill_heavy_kernel<21> : fill_heavy_kernel<16>;
   if (timer && timer->bracket(KID_FILL_FULL, &start, &stop))
     hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, start, stop, 0, P, heavy, nheavy);
   else
