@@ -466,15 +466,20 @@ __global__ __launch_bounds__(256) void fill_full_kernel(FillParams P) {
     int before = 0, nheavy = 0;
     for (int q = 0; q < 4; ++q) { const int c = wave_heavy[q]; if (q < wave) before += c; nheavy += c; }
     if (heavy) heavy_rows[before + __popcll(hm & ((1ull << lane) - 1ull))] = tid;
-    // ---- B: light rows, one thread per cell ----
-    const int cells = rows << sshift;
-    for (int c = tid; c < cells; c += 256) {
-      const int row = c >> sshift, slot = c & (P.S - 1);
+    // ---- B: light rows, one thread per four cells (16-byte stores; one table after the other) ----
+    const int quads = rows << (sshift - 2);
+    for (int c = tid; c < quads; c += 256) {
+      const int row = c >> (sshift - 2), slot = (c << 2) & (P.S - 1);
       const int d = row_deg[row];
       if (d > P.k || row_at[row] < 0) continue;
-      const int val = (slot < d) ? P.indices[row_base[row] + slot] : -1;
+      const int32_t* const from = P.indices + row_base[row] + slot;
+      int4 val = make_int4(-1, -1, -1, -1);
+      if (slot < d) val.x = from[0];
+      if (slot + 1 < d) val.y = from[1];
+      if (slot + 2 < d) val.z = from[2];
+      if (slot + 3 < d) val.w = from[3];
       const int64_t at = ((int64_t)row_at[row] << sshift) + slot;
-      for (int t = 0; t < P.ntab; ++t) P.table[t][at] = val;
+      for (int t = 0; t < P.ntab; ++t) *reinterpret_cast<int4*>(P.table[t] + at) = val;
     }
     __syncthreads();
     // ---- C: heavy rows, one W-lane group per (row, table) ----
