@@ -635,15 +635,13 @@ template <class HP>
 __device__ __forceinline__ void live_tiles_setup(const HP& P, LiveLds* L) {
   if constexpr (HP::MAX_R == 1) return;          // one relation: nothing to look up (live_count, live_tile)
   if ((int)threadIdx.x < P.R) {
-    // (P is indexed with uniform indices only: a per-lane index would move the arguments to scratch memory)
-    int dst_type = 0, src_type = 0, base = 0;
-    for (int q = 0; q < P.R; ++q)
-      if ((int)threadIdx.x == q) { dst_type = rel_of(P, q).dst_type; src_type = rel_of(P, q).src_type; base = rel_of(P, q).slot_base / TILE; }
+    // (one vector load per lane; a loop over the relations with scalar loads costs a round trip to the scalar cache each)
+    const RelParam& RP = P.rel[threadIdx.x];
+    const int dst_type = RP.dst_type, src_type = RP.src_type, base = RP.slot_base / TILE;
     L->base[threadIdx.x] = base;
     L->src_type[threadIdx.x] = src_type;
     if (threadIdx.x == 0) L->base[P.R] = P.num_tiles_ub;
-    int count = -1;
-    for (int t = 0; t < P.T; ++t) if (dst_type == t) count = type_of(P, t).count_override;
+    int count = P.type[dst_type].count_override;
     if (count < 0) count = P.state[ST_COUNTS + P.hop * P.T + dst_type];
     L->nslots[threadIdx.x] = (uint32_t)count * (uint32_t)P.f;
   }
@@ -1834,7 +1832,7 @@ __device__ __forceinline__ void tick_body(const TP& M_by_value) {
   // the slice number made the compiler copy the whole structure to scratch memory there (from 8 slices on).  The other
   // builds keep the parameter: with the pointer the 1,024-seed FCR workload ran 4 % slower.
   typedef const __attribute__((address_space(4))) TP* KernargPtr;
-  const TP& M = TP::HAS_CHAIN ? *(const TP*)(KernargPtr)__builtin_amdgcn_kernarg_segment_ptr() : M_by_value;
+  const TP& M = (TP::HAS_CHAIN || TP::Slice::MAX_R > 1) ? *(const TP*)(KernargPtr)__builtin_amdgcn_kernarg_segment_ptr() : M_by_value;
   int z = 0;
 #pragma unroll
   for (int i = 0; i < TP::SLICES - 1; ++i) z += ((int)blockIdx.x >= M.end[i]) ? 1 : 0;
