@@ -163,7 +163,7 @@ typedef struct {
                                    2 + depth / period sets (3 at least, 5 at most) when they fit 1/8 of the free device
                                    memory at gss_create, else 3, else 2 (if they fit half of it), else 1.            */
   int32_t pipeline_depth;       /* 1..GSS_MAX_IN_FLIGHT: value of gss_pipeline_depth().  Default 4 L + 2 (twice that
-                                   where a launch starts two steps; max(5, L + 2) with visit-once steps).  Every step in flight owns scratch, outputs and
+                                   where a launch may start two steps; max(5, L + 2) with visit-once steps).  Every step in flight owns scratch, outputs and
                                    (direct layout) a dedupe table.                                                    */
   int32_t steps_per_tick;       /* 1 | 2: steps a launch starts (2 only in modes that never write a table)           */
   int32_t insert_phase;         /* 1: every hop gets a separate insert phase (visit-once steps: after the place phase,
@@ -175,7 +175,7 @@ typedef struct {
                                    visit-once steps where their size allows (each node is visited by the first hop that
                                    reaches it and draws the picks of all its remaining hops there: one dependent launch
                                    per hop, the rest of the work trails behind in the launches of later steps), those of
-                                   the blocking gss_step hop by hop (sample, mark, emit per hop).  1: visit-once also
+                                   the blocking gss_step hop by hop (sample, settle per hop).  1: visit-once also
                                    in gss_step, 2: always hop by hop                                                   */
   int32_t chain_workgroups;     /* visit-once steps: most workgroups of a chain phase, which stride over the hop's nodes
                                    (1..65536; default 4096)                                                           */
@@ -208,8 +208,8 @@ gss_status gss_step(gss_sampler* s, const int32_t* seeds, int32_t num_seeds, int
 
 /* The same step split in two so that the host never idles the GPU between minibatches:
  * gss_step_async validates, plans the step, issues ONE launch (the step's first phase together with the
- * next phase of every older step in flight) and returns at once - in the modes without any refresh (FBL, OTF_FETCH)
- * on graphs with one relation only every second call launches, for the two newest steps together; in SHARED_OTF,
+ * next phase of every older step in flight) and returns at once - in the modes without a refresh per visit
+ * on graphs with one relation (with cached epochs: small graphs) mostly only every second call launches, for the two newest steps together; in SHARED_OTF,
  * whose steps are one dependent chain of launches (a step's sample or chain phases must all run before the next
  * step's first), as many launches as that chain has, so that it never waits for the host;
  * gss_step_wait issues the launches the OLDEST step in flight still needs, blocks until it has finished and

@@ -18,8 +18,8 @@
 //     tables that is not in use (there are up to five), so steps of the old epoch still in flight go on
 //     reading theirs.
 // A step with P phases is complete P ticks after it was enqueued; gss_step_wait issues the
-// missing ticks itself when fewer steps follow.  Host cost per step: one launch, which also completes the
-// finished step's event.
+// missing ticks itself when fewer steps follow.  Host cost per step: one launch (or half of
+// one).  That a launch has ended is told by the start of the next one; launches that a caller waits for complete an event.
 #include <algorithm>
 #include <atomic>
 #include <cstdarg>
@@ -733,7 +733,7 @@ void destroy_impl(gss_sampler* s) {
 
 extern "C" {
 
-const char* gss_version(void) { return "gss 0.3 (gfx950)"; }
+const char* gss_version(void) { return "gss 0.4 (gfx950)"; }
 
 const char* gss_last_error(const gss_sampler* s) { return s ? s->err : g_create_err; }
 
